@@ -180,6 +180,12 @@ __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c)
     return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
 }
 
+// (w & mask) | set in one instruction.
+__device__ __forceinline__ uint32_t bits_or(uint32_t w, uint32_t mask, uint32_t set)
+{
+    return (uint32_t)__builtin_amdgcn_bitop3_b32(w, mask, set, 0xEA);
+}
+
 __device__ __forceinline__ U4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0,
                                             uint32_t k1)
 {
