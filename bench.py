@@ -108,7 +108,7 @@ WORKLOADS = {
 # level kernels' arguments and launchers in zmc_kernels.hpp do not enter it).
 KERNEL_SOURCES = ("paper_1902_07916_amd/build.py", "paper_1902_07916_amd/csrc/zmc_sample.hip",
                   "paper_1902_07916_amd/csrc/zmc_sample_core.hpp", "paper_1902_07916_amd/csrc/zmc_integrands.hpp",
-                  "paper_1902_07916_amd/csrc/zmc_device.hpp")
+                  "paper_1902_07916_amd/csrc/zmc_trig.hpp", "paper_1902_07916_amd/csrc/zmc_device.hpp")
 TUNE_TABLE = "paper_1902_07916_amd/csrc/zmc_tune_gfx950.json"
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_sample_kernel.json")
 ISSUE_FILE = os.path.join(ROOT, "profiles", "issue_sample_kernel.json")

@@ -42,6 +42,7 @@ def hipcc() -> str:
 
 RTC_HEADERS = (("zmc.h", os.path.join(INCLUDE, "zmc.h")),
                ("zmc_device.hpp", os.path.join(CSRC, "zmc_device.hpp")),
+               ("zmc_trig.hpp", os.path.join(CSRC, "zmc_trig.hpp")),
                ("zmc_sample_core.hpp", os.path.join(CSRC, "zmc_sample_core.hpp")))
 RTC_STUBS = (("hip/hip_runtime.h", "// built into hipRTC\n"),
              ("stdint.h", "// integer types come from the hipRTC prelude\n"))

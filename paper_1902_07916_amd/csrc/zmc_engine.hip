@@ -4,6 +4,7 @@
 // and builds the next level's list.
 #include "zmc_engine.hpp"
 #include "zmc_rtc.hpp"
+#include "zmc_trig.hpp"
 
 #include <float.h>
 #include <math.h>
@@ -85,6 +86,22 @@ bool wide_ids(const zmc_request& r)
     for (int l = 0; l < r.max_depth && top <= lim; ++l)
         for (int i = 0; i < r.dim && top <= lim; ++i) top *= (unsigned __int128)split_of(r);
     return top > lim;
+}
+
+// Whether an FP64 sine or cosine of this request can meet an argument above
+// kTrigMax: its largest magnitude over the domain's corners, a hundredth
+// above for the points' rounding (a NaN parameter counts as beyond).
+bool any_argument(const zmc_request& r)
+{
+    if (r.eval != ZMC_EVAL_FP64) return false;
+    double t = 0.0;
+    if (r.integrand == ZMC_SIN_SUM) {
+        for (int i = 0; i < r.dim; ++i) t += std::max(fabs(r.lower[i]), fabs(r.upper[i]));
+    } else if (r.integrand == ZMC_GENZ_OSC) {
+        t = 6.3 * fabs(r.params[0]);
+        for (int i = 0; i < r.dim; ++i) t += fabs(r.params[1 + i]) * std::max(fabs(r.lower[i]), fabs(r.upper[i]));
+    }
+    return !(1.01 * t <= kTrigMax);
 }
 
 void set_error(const std::string& s) { g_err = s; }
@@ -230,10 +247,9 @@ int Engine::groups_of(const zmc_request& r) const { return groups_for(r, *tiles_
 
 int Engine::nch_of(const zmc_request& r) const { return chunks_for(r, *tiles_); }
 
-int Engine::capacity(int integrand, int dim, int eval, bool keep_s2, int block)
+int Engine::capacity(int integrand, int dim, int eval, int hint, int block)
 {
-    const int hint = keep_s2 ? kSumsVariant : tiles_->waves(integrand, dim, eval);
-    const int key = ((integrand * 1000 + dim * 2 + eval) * (kNumWaveHints + 1) + hint) * 8 + block / 64;
+    const int key = ((integrand * 1000 + dim * 2 + eval) * (kAnyArgVariant + 1) + hint) * 8 + block / 64;
     auto it = cap_cache_.find(key);
     if (it != cap_cache_.end()) return it->second;
     int nb = 0;
@@ -436,6 +452,7 @@ int Engine::step(hipStream_t st, const std::vector<LiveSeg>& live, uint64_t* cur
     struct Launch {
         int off, count, integrand, dim, eval;
         int64_t units, unit_samples;
+        bool any_arg;
     };
     std::vector<Launch> launches;
     for (auto& kv : buckets) {
@@ -447,9 +464,11 @@ int Engine::step(hipStream_t st, const std::vector<LiveSeg>& live, uint64_t* cur
         L.dim = r0.dim;
         L.eval = r0.eval;
         L.unit_samples = 256LL * groups_of(r0);
+        L.any_arg = false;
         int64_t u = 0;
         for (int i : kv.second) {
             const zmc_request& r = slots_[live[i].slot].req;
+            L.any_arg |= slots_[live[i].slot].any_arg;
             h_bsegs_[nb].unit_base = u;
             h_bsegs_[nb].seg = i;
             h_bsegs_[nb].pad = 0;
@@ -502,9 +521,11 @@ int Engine::step(hipStream_t st, const std::vector<LiveSeg>& live, uint64_t* cur
                 if (rc != ZMC_OK) return rc;
             } else {
                 const int block = tiles_->block(L.integrand, L.dim, L.eval);
-                const int64_t cap = capacity(L.integrand, L.dim, L.eval, sums, block);
+                const int hint = sums        ? kSumsVariant
+                                 : L.any_arg ? kAnyArgVariant
+                                             : tiles_->waves(L.integrand, L.dim, L.eval);
+                const int64_t cap = capacity(L.integrand, L.dim, L.eval, hint, block);
                 const int grid = (int)std::min<int64_t>(ceil_div(a.total_units, block / 64), cap);
-                const int hint = sums ? kSumsVariant : tiles_->waves(L.integrand, L.dim, L.eval);
                 ZMC_HIP(launch_sample(L.integrand, L.dim, L.eval, hint, grid, block, st, a));
             }
             ++n_launch;
@@ -759,6 +780,7 @@ int Engine::drive(hipStream_t st, Admission& adm, zmc_trace* trace, const std::a
             slots_[id] = in;
             HostSlot& hs = slots_[id];
             hs.wide = wide_ids(hs.req);
+            hs.any_arg = any_argument(hs.req);
             hs.level = 0;
             hs.totM = hs.totS2 = 0.0;
             reserved += hs.reserve;
@@ -857,6 +879,7 @@ int Engine::cube_estimates(const zmc_request& req, int level, const uint64_t* ui
     hs.req = req;
     init_result(hs.res);
     hs.level = level;
+    hs.any_arg = any_argument(req);
     int rc = fill_slot_desc(0, req, st);
     if (rc != ZMC_OK) return rc;
     uint64_t* d_uid = (uint64_t*)arena_.alloc(1, (size_t)n * 8);

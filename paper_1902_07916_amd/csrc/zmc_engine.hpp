@@ -105,6 +105,7 @@ struct HostSlot {
     uint64_t ticket = 0;
     size_t reserve = 0;  // serving: worst-case bytes held for it
     bool wide = false;   // its cube ids can reach 2^64 (see wide_ids)
+    bool any_arg = false; // its FP64 trigonometric arguments can exceed kTrigMax (see any_argument)
     bool cancel = false;
     std::chrono::steady_clock::time_point t_submit;
 };
@@ -123,6 +124,7 @@ int chunks_for(const zmc_request& r, const TileTable& t);
 // Worst-case device bytes of one request's tree (see Engine::reservation_bytes).
 size_t request_bytes(const zmc_request& r, const TileTable& t);
 bool wide_ids(const zmc_request& r);
+bool any_argument(const zmc_request& r);
 
 class Engine {
 public:
@@ -171,7 +173,7 @@ private:
              bool stats_only, bool want_sums);
     int next_list(hipStream_t st, std::vector<LiveSeg>& live, const std::vector<int>& split,
                   const std::vector<LiveSeg>& fresh, uint64_t*& cur_uid, int& cur_side);
-    int capacity(int integrand, int dim, int eval, bool keep_s2, int block);
+    int capacity(int integrand, int dim, int eval, int hint, int block);
     void record_level(HostSlot& hs, const SegStats& S, int64_t n, double ms, float sample_ms, int launches);
     void finish(HostSlot& hs);
 

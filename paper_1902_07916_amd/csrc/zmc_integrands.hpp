@@ -23,6 +23,7 @@
 #pragma once
 
 #include "zmc_device.hpp"
+#include "zmc_trig.hpp"
 
 namespace zmc {
 
@@ -178,13 +179,14 @@ struct Integrand<ZMC_SIN_SUM, D> {
         double scale;
     };
     __device__ static void prep64(const SlotDesc&, P64&) {}
-    __device__ static double f64(const P64&, const double* x)
+    __device__ static double arg64(const P64&, const double* x)
     {
         double t = 0.0;
 #pragma unroll
         for (int i = 0; i < D; ++i) t += x[i];
-        return sin(t);
+        return t;
     }
+    __device__ static double f64(const P64& p, const double* x) { return trig_reduced<0>(arg64(p, x)); }
     __device__ static void prep32(const SlotDesc&, const double* lo, const double* h, P32& p)
     {
         double b = 0.0;
@@ -214,13 +216,14 @@ struct Integrand<ZMC_GENZ_OSC, D> {
         p.ph = kTwoPi * sd.params[0];
         for (int i = 0; i < D; ++i) p.c[i] = sd.params[1 + i];
     }
-    __device__ static double f64(const P64& p, const double* x)
+    __device__ static double arg64(const P64& p, const double* x)
     {
         double t = p.ph;
 #pragma unroll
         for (int i = 0; i < D; ++i) t = fma(p.c[i], x[i], t);
-        return cos(t);
+        return t;
     }
+    __device__ static double f64(const P64& p, const double* x) { return trig_reduced<1>(arg64(p, x)); }
     __device__ static void prep32(const SlotDesc& sd, const double* lo, const double* h, P32& p)
     {
         double b = sd.params[0] + 0.25; // revolutions
@@ -455,6 +458,28 @@ struct Integrand<ZMC_MONOMIAL, D> {
         for (int i = 0; i < D; ++i) f *= ipow(__builtin_fmaf(p.m[i], v[i], p.b[i]), p.e[i]);
         return f;
     }
+};
+
+// ---- FP64 forms for arguments of any size -----------------------------------
+// The trigonometric families' f64 above holds for |argument| <= kTrigMax,
+// which the host knows from a request's bounds and parameters; this form
+// checks each argument (the same value wherever it is in range).  The check
+// is a branch per point around the library's reduction for huge arguments,
+// which takes registers from the whole loop: the 6-D sine needs 149 VGPRs
+// with it and 115 without.
+template <int F, int D>
+struct AnyArgument : Integrand<F, D> {};
+
+template <int D>
+struct AnyArgument<ZMC_SIN_SUM, D> : Integrand<ZMC_SIN_SUM, D> {
+    using Base = Integrand<ZMC_SIN_SUM, D>;
+    __device__ static double f64(const typename Base::P64& p, const double* x) { return sin_f64(Base::arg64(p, x)); }
+};
+
+template <int D>
+struct AnyArgument<ZMC_GENZ_OSC, D> : Integrand<ZMC_GENZ_OSC, D> {
+    using Base = Integrand<ZMC_GENZ_OSC, D>;
+    __device__ static double f64(const typename Base::P64& p, const double* x) { return cos_f64(Base::arg64(p, x)); }
 };
 
 } // namespace zmc

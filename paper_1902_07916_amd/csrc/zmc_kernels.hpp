@@ -66,6 +66,9 @@ constexpr int kNumWaveHints = 4;
 // hint value that selects the sampling kernel that also keeps the sums of
 // squares (traced levels); it runs at the compiler's default occupancy
 constexpr int kSumsVariant = kNumWaveHints;
+// hint value of the FP64 sine and cosine kernels whose arguments may exceed
+// kTrigMax (every other bucket takes its unconstrained variant for it)
+constexpr int kAnyArgVariant = kNumWaveHints + 1;
 
 // block: threads per sampling block, 64, 128 or 256 (whole waves; results
 // do not depend on it: every unit is one wave's work)

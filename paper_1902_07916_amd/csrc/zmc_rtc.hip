@@ -59,7 +59,24 @@ std::string program_source(const std::string& body, int dim, bool fp32)
     s += "#define ZMC_FP32 " + std::string(fp32 ? "true" : "false") + "\n";
     s += R"ZMCRTC(
 #include "zmc_sample_core.hpp"
+#include "zmc_trig.hpp"
 namespace zmc_user {
+// sin and cos of a double in the user's body are the registry's (other
+// argument types keep the library's)
+template <typename T> struct IsDouble { static constexpr bool value = false; };
+template <> struct IsDouble<double> { static constexpr bool value = true; };
+template <typename T>
+__device__ __forceinline__ auto sin(T t) -> decltype(::sin(t))
+{
+    if constexpr (IsDouble<T>::value) return zmc::sin_f64(t);
+    else return ::sin(t);
+}
+template <typename T>
+__device__ __forceinline__ auto cos(T t) -> decltype(::cos(t))
+{
+    if constexpr (IsDouble<T>::value) return zmc::cos_f64(t);
+    else return ::cos(t);
+}
 template <typename real>
 __device__ __forceinline__ real f(const real* x, const double* p)
 {

@@ -25,13 +25,22 @@ __global__ __launch_bounds__(kSampleThreads) __attribute__((amdgpu_waves_per_eu(
 template <int F, int D, bool FP32>
 __global__ __launch_bounds__(kSampleThreads) void sample_sums_kernel(const SampleArgs a)
 {
-    sample_units<Integrand<F, D>, D, FP32, true>(a);
+    sample_units<AnyArgument<F, D>, D, FP32, true>(a);
+}
+
+// the FP64 variant for arguments beyond the reduced range (see AnyArgument)
+template <int F, int D>
+__global__ __launch_bounds__(kSampleThreads) void sample_any_kernel(const SampleArgs a)
+{
+    sample_units<AnyArgument<F, D>, D, false, false>(a);
 }
 
 template <int F, int D, bool FP32>
 const void* ptr_dew(int hint)
 {
     static_assert(kNumWaveHints == 4, "one case per occupancy variant");
+    if constexpr (!FP32 && (F == ZMC_SIN_SUM || F == ZMC_GENZ_OSC))
+        if (hint == kAnyArgVariant) return (const void*)&sample_any_kernel<F, D>;
     switch (hint) {
     case 1: return (const void*)&sample_kernel<F, D, FP32, kWaveHints[1]>;
     case 2: return (const void*)&sample_kernel<F, D, FP32, kWaveHints[2]>;
