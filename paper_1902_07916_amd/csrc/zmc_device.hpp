@@ -18,7 +18,6 @@ namespace zmc {
 constexpr int kMaxDim = ZMC_MAX_DIM;
 constexpr int kMaxParams = ZMC_MAX_PARAMS;
 constexpr int kTileCubes = 1024;   // cubes per tile of the per-cube kernels
-constexpr int kLevelThreads = 256; // threads per block of the per-cube kernels
 
 // ---------------------------------------------------------------------------
 // Device-resident tables (structure of arrays where per-cube, small structs
@@ -260,6 +259,92 @@ __device__ __forceinline__ float unit_interval_f32(uint32_t w)
 {
     return __uint_as_float(__builtin_amdgcn_alignbit(0x7Fu, w, 9u));
 }
+
+// ---------------------------------------------------------------------------
+// Reductions over a wave of 64 lanes: op over the pairs of lanes 32, 16, 8, 4,
+// 2 and 1 apart, every lane ending with the result.  The halves and the odd
+// and even rows of 16 change places by v_permlane32_swap / v_permlane16_swap,
+// the rest by rotations within a row (after the step before, a row's values
+// repeat at twice the distance, so rotating reaches the partner).  These are
+// vector instructions; the same butterfly over ds_bpermute (__shfl_xor) waits
+// for LDS in each of its six dependent steps.
+// ---------------------------------------------------------------------------
+template <int CTRL>
+__device__ __forceinline__ uint32_t row_move(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
+}
+
+struct WavePair {
+    uint64_t a, b;
+};
+
+__device__ __forceinline__ WavePair swap_halves(uint64_t v)
+{
+    const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)v, (uint32_t)v, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(v >> 32), (uint32_t)(v >> 32), false, false);
+    return WavePair{(uint64_t)hi[0] << 32 | lo[0], (uint64_t)hi[1] << 32 | lo[1]};
+}
+
+__device__ __forceinline__ WavePair swap_rows(uint64_t v)
+{
+    const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)v, (uint32_t)v, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(v >> 32), (uint32_t)(v >> 32), false, false);
+    return WavePair{(uint64_t)hi[0] << 32 | lo[0], (uint64_t)hi[1] << 32 | lo[1]};
+}
+
+template <class T>
+__device__ __forceinline__ uint64_t to_bits(T v)
+{
+    static_assert(sizeof(T) == 8, "64-bit values");
+    return __builtin_bit_cast(uint64_t, v);
+}
+
+template <class T>
+__device__ __forceinline__ T from_bits(uint64_t v)
+{
+    return __builtin_bit_cast(T, v);
+}
+
+template <int CTRL, class T>
+__device__ __forceinline__ T row_rotated(T v)
+{
+    const uint64_t b = to_bits(v);
+    return from_bits<T>((uint64_t)row_move<CTRL>((uint32_t)(b >> 32)) << 32 | row_move<CTRL>((uint32_t)b));
+}
+
+// Over each N consecutive lanes of a row of 16 (the values repeat every N).
+template <int N = 16, class T, class Op>
+__device__ __forceinline__ T row_reduce(T v, Op op)
+{
+    if constexpr (N >= 16) v = op(v, row_rotated<0x128>(v));
+    if constexpr (N >= 8) v = op(v, row_rotated<0x124>(v));
+    if constexpr (N >= 4) v = op(v, row_rotated<0x122>(v));
+    return op(v, row_rotated<0x121>(v));
+}
+
+template <class T, class Op>
+__device__ __forceinline__ T wave_reduce(T v, Op op)
+{
+    WavePair p = swap_halves(to_bits(v));
+    v = op(from_bits<T>(p.a), from_bits<T>(p.b));
+    p = swap_rows(to_bits(v));
+    v = op(from_bits<T>(p.a), from_bits<T>(p.b));
+    return row_reduce(v, op);
+}
+
+struct OpAdd {
+    template <class T>
+    __device__ __forceinline__ T operator()(T a, T b) const { return a + b; }
+};
+struct OpMin {
+    __device__ __forceinline__ double operator()(double a, double b) const { return fmin(a, b); }
+};
+struct OpMax {
+    __device__ __forceinline__ double operator()(double a, double b) const { return fmax(a, b); }
+};
+
+__device__ __forceinline__ double wave_sum(double v) { return wave_reduce(v, OpAdd{}); }
 
 // ---------------------------------------------------------------------------
 // Geometry of cube (uid, level): lattice cell K_i on a grid of d*b^level

@@ -14,7 +14,7 @@
 // an L2 write-back per block, which outweighs a launch once a level has a few
 // hundred tiles; large levels therefore run the per-segment steps as their own
 // one-block-per-segment launches.  Every reduction has a fixed shape (thread-serial over its
-// elements, then wave64 butterflies, then the 4 waves in order), so results
+// elements, then a butterfly in each wave, then one over the waves), so results
 // are bitwise reproducible and independent of which block finishes last or
 // of what else is resident.
 #include <float.h>
@@ -27,85 +27,32 @@ namespace zmc {
 
 namespace {
 
+constexpr int kLevelThreads = 256; // threads per block of the per-cube kernels
 constexpr int kWaves = kLevelThreads / 64;
 constexpr int kPerThread = kTileCubes / kLevelThreads;
 
-__device__ __forceinline__ double wave_sum(double v)
+// Block-wide reductions in a fixed order, every thread getting the result: a
+// butterfly in each wave, then one over the waves' values.
+template <class T, class Op>
+__device__ __forceinline__ T over_waves(const T* sh, Op op)
 {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
+    static_assert(kWaves == 4 || kWaves == 8 || kWaves == 16, "the waves' values repeat within a row of lanes");
+    return row_reduce<kWaves>(sh[threadIdx.x & (kWaves - 1)], op);
 }
 
-__device__ __forceinline__ double wave_min(double v)
+template <class T, class Op>
+__device__ __forceinline__ T block_reduce(T v, T* sh, Op op)
 {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v = fmin(v, __shfl_xor(v, off, 64));
-    return v;
-}
-
-__device__ __forceinline__ double wave_max(double v)
-{
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
-    return v;
-}
-
-__device__ __forceinline__ int64_t wave_sum_i(int64_t v)
-{
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
-
-// Block-wide sum in a fixed order; every thread gets the result.
-__device__ double block_sum(double v, double* sh)
-{
-    v = wave_sum(v);
+    v = wave_reduce(v, op);
     __syncthreads();
     if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
     __syncthreads();
-    double t = sh[0];
-#pragma unroll
-    for (int w = 1; w < kWaves; ++w) t += sh[w];
-    return t;
+    return over_waves(sh, op);
 }
 
-__device__ double block_min(double v, double* sh)
-{
-    v = wave_min(v);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
-    __syncthreads();
-    double t = sh[0];
-#pragma unroll
-    for (int w = 1; w < kWaves; ++w) t = fmin(t, sh[w]);
-    return t;
-}
-
-__device__ double block_max(double v, double* sh)
-{
-    v = wave_max(v);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
-    __syncthreads();
-    double t = sh[0];
-#pragma unroll
-    for (int w = 1; w < kWaves; ++w) t = fmax(t, sh[w]);
-    return t;
-}
-
-__device__ int64_t block_sum_i(int64_t v, int64_t* sh)
-{
-    v = wave_sum_i(v);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
-    __syncthreads();
-    int64_t t = 0;
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) t += sh[w];
-    return t;
-}
+__device__ __forceinline__ double block_sum(double v, double* sh) { return block_reduce(v, sh, OpAdd{}); }
+__device__ __forceinline__ double block_min(double v, double* sh) { return block_reduce(v, sh, OpMin{}); }
+__device__ __forceinline__ double block_max(double v, double* sh) { return block_reduce(v, sh, OpMax{}); }
 
 // The selection totals of a tile or a segment, reduced over the block in one
 // exchange: four sums, a minimum and a count, each combined in the same
@@ -117,35 +64,27 @@ struct SelTotals {
 
 __device__ SelTotals block_reduce_sel(SelTotals v)
 {
-    __shared__ double shd[kWaves][5];
+    __shared__ double shd[5][kWaves];
     __shared__ int64_t shn[kWaves];
     v.accM = wave_sum(v.accM);
     v.accS2 = wave_sum(v.accS2);
     v.selM = wave_sum(v.selM);
     v.selS2 = wave_sum(v.selS2);
-    v.margin = wave_min(v.margin);
-    v.nsel = wave_sum_i(v.nsel);
+    v.margin = wave_reduce(v.margin, OpMin{});
+    v.nsel = wave_reduce(v.nsel, OpAdd{});
     __syncthreads();
     if ((threadIdx.x & 63) == 0) {
         const int w = threadIdx.x >> 6;
-        shd[w][0] = v.accM;
-        shd[w][1] = v.accS2;
-        shd[w][2] = v.selM;
-        shd[w][3] = v.selS2;
-        shd[w][4] = v.margin;
+        shd[0][w] = v.accM;
+        shd[1][w] = v.accS2;
+        shd[2][w] = v.selM;
+        shd[3][w] = v.selS2;
+        shd[4][w] = v.margin;
         shn[w] = v.nsel;
     }
     __syncthreads();
-    SelTotals t{shd[0][0], shd[0][1], shd[0][2], shd[0][3], shd[0][4], 0};
-    for (int w = 1; w < kWaves; ++w) {
-        t.accM += shd[w][0];
-        t.accS2 += shd[w][1];
-        t.selM += shd[w][2];
-        t.selS2 += shd[w][3];
-        t.margin = fmin(t.margin, shd[w][4]);
-    }
-    for (int w = 0; w < kWaves; ++w) t.nsel += shn[w];
-    return t;
+    return SelTotals{over_waves(shd[0], OpAdd{}), over_waves(shd[1], OpAdd{}), over_waves(shd[2], OpAdd{}),
+                     over_waves(shd[3], OpAdd{}), over_waves(shd[4], OpMin{}), over_waves(shn, OpAdd{})};
 }
 
 // Exclusive prefix of a 0/1 flag over the block in thread order; *total gets
@@ -247,9 +186,25 @@ __device__ void seg_thr(const LevelArgs& a, int si)
     }
 }
 
+// What the decision reads besides the totals.  Loaded before the reductions:
+// the last step of a level is one thread's, and each of these would be a
+// memory latency of its own there.
+struct DecideIn {
+    double2 prev;
+    double rtol;
+    int64_t max_cubes;
+    int32_t trials, kids, range_lost;
+};
+
+__device__ __forceinline__ DecideIn decide_in(const LevelArgs& a, int si)
+{
+    const SlotDesc& sd = a.slots[a.segs[si].slot];
+    return DecideIn{a.prev_tot[si], sd.rtol, sd.max_cubes, sd.trials, sd.kids, a.seg_flags ? a.seg_flags[si] : 0};
+}
+
 __device__ void seg_decide(const LevelArgs& a, int si);
-__device__ void decide_write(const LevelArgs& a, int si, double accM, double accS2, double selM, double selS2,
-                             double margin, int64_t nsel, int bad);
+__device__ void decide_write(const LevelArgs& a, int si, const DecideIn& in, double accM, double accS2, double selM,
+                             double selS2, double margin, int64_t nsel, int bad);
 
 // ---- finalize: per cube I_t = V * S1_t / N, m = mean I_t, s = std I_t ------
 // The partial sums of 256 consecutive cubes are contiguous ([cube][trial *
@@ -376,10 +331,10 @@ __device__ void sqdev_tile(const LevelArgs& a, int64_t tile, int si)
     const int e = thr_scale_exp(mu, a.stats[si].s_min, a.stats[si].s_max);
     const int64_t first = (tile - sg.tile_base) * kTileCubes;
     double acc = 0.0;
+#pragma unroll
     for (int j = 0; j < kPerThread; ++j) {
         const int64_t cl = first + threadIdx.x + (int64_t)j * kLevelThreads;
-        if (cl >= sg.n_cubes) break;
-        const double d = ldexp(a.s[sg.cube_base + cl] - mu, -e);
+        const double d = cl < sg.n_cubes ? ldexp(a.s[sg.cube_base + cl] - mu, -e) : 0.0;
         acc += d * d;
     }
     const double tot = block_sum(acc, sh);
@@ -440,7 +395,7 @@ __global__ __launch_bounds__(kLevelThreads) void group_thr_kernel(const LevelArg
         const double mu = wave_sum(v) / (double)gs;
         double dmax = 0.0;
         for (int64_t j = lane; j < gs; j += 64) dmax = fmax(dmax, fabs(s[j] - mu));
-        const int e = std_scale_exp(wave_max(dmax));
+        const int e = std_scale_exp(wave_reduce(dmax, OpMax{}));
         double q = 0.0;
         for (int64_t j = lane; j < gs; j += 64) {
             const double d = ldexp(s[j] - mu, -e);
@@ -460,6 +415,7 @@ __device__ void select_tile(const LevelArgs& a, int64_t tile, int si)
     const int64_t first = (tile - sg.tile_base) * kTileCubes;
     double accM = 0.0, accS2 = 0.0, selM = 0.0, selS2 = 0.0, margin = DBL_MAX;
     int64_t nsel = 0;
+#pragma unroll
     for (int j = 0; j < kPerThread; ++j) {
         const int64_t cl = first + threadIdx.x + (int64_t)j * kLevelThreads;
         if (cl >= sg.n_cubes) break;
@@ -504,7 +460,7 @@ __device__ void seg_decide(const LevelArgs& a, int si)
 {
     __shared__ int64_t shi[kWaves];
     const Segment& sg = a.segs[si];
-    const SlotDesc& sd = a.slots[sg.slot];
+    const DecideIn in = decide_in(a, si);
     double accM = 0.0, accS2 = 0.0, selM = 0.0, selS2 = 0.0, margin = DBL_MAX;
     int64_t nsel = 0;
     int bad = 0;
@@ -555,19 +511,17 @@ __device__ void seg_decide(const LevelArgs& a, int si)
         carry += chunk;
     }
 
-    if (threadIdx.x == 0) decide_write(a, si, accM, accS2, selM, selS2, margin, nsel, bad);
+    if (threadIdx.x == 0) decide_write(a, si, in, accM, accS2, selM, selS2, margin, nsel, bad);
 }
 
 // The segment's outcome from its totals (thread 0): stop rules, running
 // totals, the record in device memory and in the mapped host buffer.
-__device__ void decide_write(const LevelArgs& a, int si, double accM, double accS2, double selM, double selS2,
-                             double margin, int64_t nsel, int bad)
+__device__ void decide_write(const LevelArgs& a, int si, const DecideIn& in, double accM, double accS2, double selM,
+                             double selS2, double margin, int64_t nsel, int bad)
 {
     const Segment& sg = a.segs[si];
-    const SlotDesc& sd = a.slots[sg.slot];
     {
         SegStats& S = a.stats[si];
-        const double2 prev = a.prev_tot[si];
         if (!sg.need_thr || sg.group_size) {
             S.mu = S.sd = S.thr = __builtin_nan("");
         }
@@ -578,16 +532,16 @@ __device__ void decide_write(const LevelArgs& a, int si, double accM, double acc
         S.selS2 = selS2;
         S.n_sel = nsel;
         S.nonfinite = bad;
-        S.range_lost = a.seg_flags ? a.seg_flags[si] : 0;
+        S.range_lost = in.range_lost;
         int32_t dec;
-        double totM = prev.x + accM, totS2 = prev.y + accS2;
+        double totM = in.prev.x + accM, totS2 = in.prev.y + accS2;
         if (!sg.need_thr || nsel == 0) {
             dec = kDone;
         } else {
             const double runM = totM + selM, runS2 = totS2 + selS2;
-            if (sd.rtol > 0.0 && sqrt(runS2 / (double)(sd.trials - 1)) <= sd.rtol * fabs(runM)) {
+            if (in.rtol > 0.0 && sqrt(runS2 / (double)(in.trials - 1)) <= in.rtol * fabs(runM)) {
                 dec = kRtolMet;
-            } else if ((uint64_t)nsel * (uint64_t)sd.kids > (uint64_t)sd.max_cubes) {
+            } else if ((uint64_t)nsel * (uint64_t)in.kids > (uint64_t)in.max_cubes) {
                 dec = kTruncated;
             } else {
                 dec = kSplit;
@@ -625,6 +579,8 @@ __global__ __launch_bounds__(kLevelThreads) void level_small_kernel(const LevelA
     const Segment& sg = a.segs[si];
     const int64_t tile = sg.tile_base;
     const bool thr_on = sg.need_thr != 0;
+    const DecideIn in = decide_in(a, si);
+    const double sigma_mult = a.slots[sg.slot].sigma_mult;
     double m_r[kPerThread], s_r[kPerThread];
     double tot_s = 0.0, s_ext[2] = {0.0, 0.0};
     int bad = 0;
@@ -637,15 +593,12 @@ __global__ __launch_bounds__(kLevelThreads) void level_small_kernel(const LevelA
         double acc = 0.0;
 #pragma unroll
         for (int j = 0; j < kPerThread; ++j) {
-            const int64_t cl = threadIdx.x + (int64_t)j * kLevelThreads;
-            if (cl < n) {
-                const double d = ldexp(s_r[j] - mu, -e);
-                acc += d * d;
-            }
+            const double d = (int64_t)threadIdx.x + j * kLevelThreads < n ? ldexp(s_r[j] - mu, -e) : 0.0;
+            acc += d * d;
         }
         tot_sq = block_sum(acc, sh);
         sdv = ldexp(sqrt(tot_sq / (double)n), e);
-        thr = mu + a.slots[sg.slot].sigma_mult * sdv;
+        thr = mu + sigma_mult * sdv;
     }
     double accM = 0.0, accS2 = 0.0, selM = 0.0, selS2 = 0.0, margin = DBL_MAX;
     int64_t nsel = 0;
@@ -685,7 +638,7 @@ __global__ __launch_bounds__(kLevelThreads) void level_small_kernel(const LevelA
             a.stats[si].sd = sdv;
             a.stats[si].thr = thr;
         }
-        decide_write(a, si, tot.accM, tot.accS2, tot.selM, tot.selS2, tot.margin, tot.nsel, bad);
+        decide_write(a, si, in, tot.accM, tot.accS2, tot.selM, tot.selS2, tot.margin, tot.nsel, bad);
     }
 }
 
@@ -703,15 +656,21 @@ __device__ void spawn_tile(const LevelArgs& a, int64_t tile)
     const int D = sd.dim;
     const int64_t kids = sd.kids;
     const int64_t first = (tile - sg.tile_base) * kTileCubes;
-    int base = 0;
+    int flags[kPerThread];
+#pragma unroll
     for (int j = 0; j < kPerThread; ++j) {
         const int64_t cl = first + threadIdx.x + (int64_t)j * kLevelThreads;
-        const int flag = (cl < sg.n_cubes) ? a.sel[sg.cube_base + cl] : 0;
+        flags[j] = (cl < sg.n_cubes) ? a.sel[sg.cube_base + cl] : 0;
+    }
+    int base = 0;
+#pragma unroll
+    for (int j = 0; j < kPerThread; ++j) {
         int total;
-        const int pos = block_excl_scan_flag(flag, shf, &total);
-        if (flag) {
-            list[base + pos] = a.uid[sg.cube_base + cl];
-            list_hi[base + pos] = a.uid_hi ? a.uid_hi[sg.cube_base + cl] : 0u;
+        const int pos = block_excl_scan_flag(flags[j], shf, &total);
+        if (flags[j]) {
+            const int64_t c = sg.cube_base + first + threadIdx.x + (int64_t)j * kLevelThreads;
+            list[base + pos] = a.uid[c];
+            list_hi[base + pos] = a.uid_hi ? a.uid_hi[c] : 0u;
         }
         base += total;
     }

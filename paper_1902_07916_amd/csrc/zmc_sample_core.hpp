@@ -28,14 +28,6 @@
 
 namespace zmc {
 
-
-__device__ __forceinline__ double wave_sum(double v)
-{
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
-
 template <int D>
 __device__ __forceinline__ void corner(const SlotDesc& sd, int level, uint64_t uid, uint32_t uid_hi, double* lo,
                                        double* h)
