@@ -5,7 +5,7 @@
 //
 // All of these are HBM-bound and small next to the sampling kernel.  The
 // per-cube kernels work on tiles of 1024 consecutive cubes of one segment
-// (256 threads, 4 cubes each, strided so that loads coalesce).  The
+// (512 threads, 2 cubes each, strided so that loads coalesce).  The
 // per-integral step that follows each of them (the mean of s, the threshold,
 // the decision) runs, for small levels, in the same launch: the last tile
 // block of a segment to finish, found with a per-segment counter, reduces
@@ -27,7 +27,12 @@ namespace zmc {
 
 namespace {
 
-constexpr int kLevelThreads = 256; // threads per block of the per-cube kernels
+// Threads per block of the per-cube kernels, two cubes of a tile each.  A small
+// level has few tiles and waits for each block's chain of loads, divisions and
+// reductions: finalize over 8 tiles takes 18.0 us with 256 threads, 13.5 with
+// 512 and 13.5 with 1024, the selection 8.7, 9.8 and 13.2 (its barriers wait
+// for more waves); over 464 tiles finalize takes 35, 27 and 48.
+constexpr int kLevelThreads = 512;
 constexpr int kWaves = kLevelThreads / 64;
 constexpr int kPerThread = kTileCubes / kLevelThreads;
 
@@ -207,11 +212,15 @@ __device__ void decide_write(const LevelArgs& a, int si, const DecideIn& in, dou
                              double selS2, double margin, int64_t nsel, int bad);
 
 // ---- finalize: per cube I_t = V * S1_t / N, m = mean I_t, s = std I_t ------
-// The partial sums of 256 consecutive cubes are contiguous ([cube][trial *
-// nch + chunk]); when they fit kStage pairs, the block first copies them to
-// LDS with coalesced loads, and each thread then reads its own cube's row
-// there.  Larger rows (many trials or chunks) are read from memory directly.
-constexpr int kStage = 2560; // 40 KiB of (S1, S2) pairs
+// The partial sums of a pass's cubes are contiguous ([cube][trial *
+// nch + chunk]); when their S1 members fit kStage values, the block first
+// copies those to LDS with coalesced loads, and each thread then reads its own
+// cube's row there.  The row then takes the trial values I_t, so that the
+// division and the product of each are done once and not again for the
+// deviations.  Wider rows (many trials or chunks) are read from memory, only
+// their trial values kept in LDS, or formed again for each of the three sums
+// where those do not fit either.
+constexpr int kStage = 5120; // 40 KiB of doubles: rows of up to 10 values
 
 // KEEP: also leave each thread's cubes' m and s in m_r / s_r (pass j at
 // index j), for the one-block level path.
@@ -223,12 +232,13 @@ __device__ void finalize_tile(const LevelArgs& a, int64_t tile, int si, double* 
                               double* s_ext = nullptr)
 {
     __shared__ double sh[kWaves];
-    __shared__ double2 stage[kStage];
+    __shared__ double stage[kStage];
     const Segment& sg = a.segs[si];
     const SlotDesc& sd = a.slots[sg.slot];
     const int D = sd.dim, n1 = sd.trials, nch = sd.nch;
-    const int per = n1 * nch; // pairs per cube
+    const int per = n1 * nch; // partials per cube
     const bool staged = per * kLevelThreads <= kStage;
+    const bool rows = n1 * kLevelThreads <= kStage; // the trial values fit LDS
     const double V = cube_volume(sd, D, sg.level);
     const double N = (double)sd.samples;
     const int64_t first = (tile - sg.tile_base) * kTileCubes;
@@ -239,47 +249,53 @@ __device__ void finalize_tile(const LevelArgs& a, int64_t tile, int si, double* 
         const int64_t c0 = first + (int64_t)j * kLevelThreads; // first cube of this pass
         if (c0 >= sg.n_cubes) break;                            // uniform over the block
         const int cnt = (int)min<int64_t>(kLevelThreads, sg.n_cubes - c0);
-        const double2* P;
+        const double2* src = a.partial + sg.part_base + c0 * per;
         if (staged) {
-            const double2* src = a.partial + sg.part_base + c0 * per;
             __syncthreads(); // the previous pass is done with the stage
-            for (int e = threadIdx.x; e < cnt * per; e += kLevelThreads) stage[e] = src[e];
+            for (int e = threadIdx.x; e < cnt * per; e += kLevelThreads) stage[e] = src[e].x;
             __syncthreads();
-            P = stage + threadIdx.x * per;
-        } else {
-            P = a.partial + sg.part_base + (c0 + threadIdx.x) * per;
         }
         if ((int)threadIdx.x >= cnt) continue;
         const int64_t cl = c0 + threadIdx.x;
         const int64_t c = sg.cube_base + cl;
-        double sum = 0.0;
-        for (int t = 0; t < n1; ++t) {
-            double S1 = 0.0, S2 = 0.0;
-            for (int ch = 0; ch < nch; ++ch) {
-                const double2 v = P[t * nch + ch];
-                S1 += v.x;
-                S2 += v.y;
-            }
-            if (a.tr_S1) {
-                a.tr_S1[c * n1 + t] = S1;
+        const double2* P = src + (int64_t)threadIdx.x * per;
+        double* row = stage + threadIdx.x * (staged ? per : n1); // this thread's alone from here on
+        auto S1_mem = [&](int t) {
+            double S1 = 0.0;
+            for (int ch = 0; ch < nch; ++ch) S1 += P[t * nch + ch].x;
+            return S1;
+        };
+        if (a.tr_S1) {
+            for (int t = 0; t < n1; ++t) {
+                double S2 = 0.0;
+                for (int ch = 0; ch < nch; ++ch) S2 += P[t * nch + ch].y;
+                a.tr_S1[c * n1 + t] = S1_mem(t);
                 a.tr_S2[c * n1 + t] = S2;
             }
-            sum += V * (S1 / N);
         }
+        double sum = 0.0;
+        for (int t = 0; t < n1; ++t) {
+            double S1 = 0.0;
+            if (staged) {
+                for (int ch = 0; ch < nch; ++ch) S1 += row[t * nch + ch];
+            } else {
+                S1 = S1_mem(t);
+            }
+            const double I = V * (S1 / N);
+            if (rows) row[t] = I; // among the row's partials already read
+            sum += I;
+        }
+        auto value = [&](int t) { return rows ? row[t] : V * (S1_mem(t) / N); };
         const double m = sum / (double)n1;
         double dmax = 0.0;
         for (int t = 0; t < n1; ++t) {
-            double S1 = 0.0;
-            for (int ch = 0; ch < nch; ++ch) S1 += P[t * nch + ch].x;
-            const double d = fabs(V * (S1 / N) - m);
+            const double d = fabs(value(t) - m);
             if (d > dmax) dmax = d;
         }
         const int e = std_scale_exp(dmax);
         double ss = 0.0;
         for (int t = 0; t < n1; ++t) {
-            double S1 = 0.0;
-            for (int ch = 0; ch < nch; ++ch) S1 += P[t * nch + ch].x;
-            const double d = ldexp(V * (S1 / N) - m, -e);
+            const double d = ldexp(value(t) - m, -e);
             ss += d * d;
         }
         const double s = ldexp(sqrt(ss / (double)n1), e);
