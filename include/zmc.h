@@ -46,8 +46,8 @@
  *    library never allocates or frees device memory itself (it allocates
  *    pinned host staging buffers);
  *  - `stream` is a hipStream_t owned by the caller (NULL = the default
- *    stream); the library enqueues on it and, for synchronous calls,
- *    synchronises it before returning.
+ *    stream); the library enqueues on it and, for synchronous calls, waits
+ *    for its work there before returning.
  */
 #ifndef ZMC_H
 #define ZMC_H
@@ -140,8 +140,9 @@ typedef struct {
     double min_margin_per_level[ZMC_MAX_LEVELS]; /* min |s - thr| / thr        */
     float ms_per_level[ZMC_MAX_LEVELS];          /* wall time of each level    */
     float sample_ms_per_level[ZMC_MAX_LEVELS];   /* GPU time of the level's
-                                                    sampling launches (HIP
-                                                    events on the stream)      */
+                                                    sampling launches (device
+                                                    clock, first launch's start
+                                                    to the next kernel's)      */
     int32_t sample_launches_per_level[ZMC_MAX_LEVELS];
     double latency_ms; /* serving: submit -> completion; otherwise call time */
 } zmc_result;
@@ -271,8 +272,8 @@ int zmc_integrate_request(const zmc_request* req, void* stream, zmc_result* out,
  * those of zmc_integrate_request() (the same kernels).  Calls share that one
  * array and keep no state in it between calls (the level counters it holds
  * are left at zero by every launch); the library serialises them, and each
- * call synchronises its stream before returning, so calls do not overlap on
- * the device: a caller that replays such a call asynchronously (e.g. from a
+ * call waits for its last kernel's records before returning, so calls do not
+ * overlap on the device: a caller that replays such a call asynchronously (e.g. from a
  * captured graph) must not let two of them run at once.
  * ENOMEM (before any device work, with the sizes in zmc_strerror) when the
  * request's worst-case tree (zmc_request_bytes) exceeds the static array;

@@ -296,7 +296,7 @@ void server_main(Server* S, Lane* L, int device)
         std::lock_guard<std::mutex> lk(S->mu);
         return S->cancelled.count(t) > 0;
     };
-    int rc = L->eng.drive(L->st, adm, nullptr, &S->stop, &S->n_levels);
+    int rc = L->eng.drive(L->st, L->eng.max_slots(), adm, nullptr, &S->stop, &S->n_levels);
     std::lock_guard<std::mutex> lk(S->mu);
     if (rc != ZMC_OK && S->rc == ZMC_OK) S->rc = rc;
     if (rc != ZMC_OK) {

@@ -105,7 +105,11 @@ struct SampleArgs {
     int32_t* seg_flags;  // per segment of the level (0 at the level's start):
                          // kRangeLost when an FP32 unit's sum fell below
                          // FP32's normal range
+    uint64_t* clock;     // mapped host memory: the level's first launch notes when it began (else NULL)
 };
+
+// The device's constant-rate clock.
+__device__ __forceinline__ uint64_t device_clock() { return __builtin_amdgcn_s_memrealtime(); }
 
 // seg_flags / SegStats::range_lost: some sampling unit's FP32 values summed
 // to less than (points of the unit) * 2^-126 in magnitude, i.e. they lay

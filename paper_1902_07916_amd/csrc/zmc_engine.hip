@@ -42,6 +42,23 @@ size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 // pays an L2 write-back to publish its tile record).
 constexpr int64_t kFuseMaxTiles = 256;
 
+// A level whose table takes at most kDirectTable bytes, with at most
+// CopyArgs::kMaxSlots new integrals and kFuseMaxTiles tiles to spawn from, is
+// uploaded by the next-list kernel itself: it reads the host's mapped staging
+// memory and copies it to the device for the kernels after it.  That takes a
+// copy command out of the level's chain of dependent commands (and a second
+// one for each new integral).  Larger tables are read by many blocks, whose
+// binary searches over the segments should not cross the bus.  With the wait
+// and the clocks below, a level of three short kernels takes 11.6 us from the
+// first launch to the host seeing its end, against 26.7 with a copy command,
+// two events around the sampling and a stream synchronisation.
+constexpr size_t kDirectTable = 4096;
+
+// The host watches for a level's records in mapped memory this long before it
+// blocks in the runtime.  Watching sees a short level's end 4-5 us sooner; a
+// level that takes longer loses nothing by the wait.
+constexpr double kWatchMs = 0.2;
+
 // Packed per-level tables: segments at 0, running totals, bucket segments,
 // per-segment flags (uploaded as zeros), then the segments of the previous
 // level's spawn and of the new roots (at most two per slot).
@@ -194,25 +211,35 @@ int Engine::setup(char* base, size_t bytes, int max_slots, const TileTable* tile
     arena_.init(base + off, bytes - off);
     // the tile counters start at 0 and every launch leaves them at 0
     ZMC_HIP(hipMemset(d_seg_count_, 0, sizeof(int32_t) * max_slots));
-    ZMC_HIP(hipHostMalloc((void**)&h_slots_, sizeof(SlotDesc) * max_slots, hipHostMallocDefault));
-    ZMC_HIP(hipHostMalloc((void**)&h_tab_, tab_bytes_, hipHostMallocDefault));
+    ZMC_HIP(hipHostMalloc((void**)&h_slots_, sizeof(SlotDesc) * max_slots, hipHostMallocMapped));
+    ZMC_HIP(hipHostGetDevicePointer((void**)&d_hslots_, h_slots_, 0));
+    ZMC_HIP(hipHostMalloc((void**)&h_tab_, tab_bytes_, hipHostMallocMapped));
+    ZMC_HIP(hipHostGetDevicePointer((void**)&d_htab_, h_tab_, 0));
     ZMC_HIP(hipHostMalloc((void**)&h_nextsegs_, sizeof(Segment) * 2 * max_slots, hipHostMallocDefault));
     // the decision kernel writes each level's per-segment records straight
-    // into this mapped host buffer, read after the level's synchronisation
+    // into this mapped host buffer, read once the level's number is there
     ZMC_HIP(hipHostMalloc((void**)&h_stats_, sizeof(SegStats) * max_slots, hipHostMallocMapped));
     ZMC_HIP(hipHostGetDevicePointer((void**)&d_hstats_, h_stats_, 0));
+    ZMC_HIP(hipHostMalloc((void**)&h_seq_, sizeof(uint32_t) * max_slots, hipHostMallocMapped));
+    ZMC_HIP(hipHostGetDevicePointer((void**)&d_hseq_, (void*)h_seq_, 0));
+    memset((void*)h_seq_, 0, sizeof(uint32_t) * max_slots);
+    ZMC_HIP(hipHostMalloc((void**)&h_clock_, 2 * sizeof(uint64_t), hipHostMallocMapped));
+    ZMC_HIP(hipHostGetDevicePointer((void**)&d_hclock_, (void*)h_clock_, 0));
+    h_clock_[0] = h_clock_[1] = 0;
+    seq_ = 0;
     h_segs_ = (Segment*)h_tab_;
     d_segs_ = (Segment*)d_tab_;
     ZMC_HIP(hipDeviceGetAttribute(&n_cu_, hipDeviceAttributeMultiprocessorCount, device));
-    ZMC_HIP(hipEventCreate(&ev_sample0_));
-    ZMC_HIP(hipEventCreate(&ev_sample1_));
+    int khz = 0;
+    if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, device) == hipSuccess && khz > 0)
+        clock_ms_ = 1.0 / (double)khz;
     slots_.assign(max_slots, HostSlot());
     return ZMC_OK;
 }
 
 void Engine::teardown()
 {
-    void* hs[] = {h_slots_, h_tab_, h_nextsegs_, h_stats_};
+    void* hs[] = {h_slots_, h_tab_, h_nextsegs_, h_stats_, (void*)h_seq_, (void*)h_clock_};
     for (void* p : hs)
         if (p) (void)hipHostFree(p);
     h_slots_ = nullptr;
@@ -221,9 +248,13 @@ void Engine::teardown()
     h_bsegs_ = nullptr;
     h_stats_ = d_hstats_ = nullptr;
     h_prev_ = nullptr;
-    if (ev_sample0_) (void)hipEventDestroy(ev_sample0_);
-    if (ev_sample1_) (void)hipEventDestroy(ev_sample1_);
-    ev_sample0_ = ev_sample1_ = nullptr;
+    h_seq_ = nullptr;
+    h_clock_ = nullptr;
+    d_htab_ = nullptr;
+    d_hslots_ = nullptr;
+    d_hseq_ = nullptr;
+    d_hclock_ = nullptr;
+    pend_slots_.clear();
     slots_.clear();
     cap_cache_.clear();
 }
@@ -261,7 +292,7 @@ int Engine::capacity(int integrand, int dim, int eval, int hint, int block)
     return cap;
 }
 
-int Engine::fill_slot_desc(int slot, const zmc_request& r, hipStream_t st)
+void Engine::fill_slot_desc(int slot, const zmc_request& r)
 {
     SlotDesc& d = h_slots_[slot];
     memset(&d, 0, sizeof(d));
@@ -286,7 +317,40 @@ int Engine::fill_slot_desc(int slot, const zmc_request& r, hipStream_t st)
         d.h0[i] = (r.upper[i] - r.lower[i]) / (double)r.divisions_per_axis;
     }
     for (int j = 0; j < r.n_params && j < ZMC_MAX_PARAMS; ++j) d.params[j] = r.params[j];
-    ZMC_HIP(hipMemcpyAsync(d_slots_ + slot, &d, sizeof(SlotDesc), hipMemcpyHostToDevice, st));
+}
+
+int Engine::upload_slot(int slot, hipStream_t st)
+{
+    ZMC_HIP(hipMemcpyAsync(d_slots_ + slot, h_slots_ + slot, sizeof(SlotDesc), hipMemcpyHostToDevice, st));
+    return ZMC_OK;
+}
+
+// Wait for the records of the level just launched (ns segments).  The kernels
+// write each segment's record and then the level's number into mapped host
+// memory; they are the level's last, so once every number is there nothing
+// of the level is outstanding.
+int Engine::wait_level(hipStream_t st, int ns)
+{
+    const double t0 = now_ms();
+    int i = 0;
+    while (true) {
+        for (int spin = 0; spin < 64 && i < ns; ++spin) {
+            if (h_seq_[i] == seq_) ++i, spin = 0;
+            else __builtin_ia32_pause();
+        }
+        if (i == ns) {
+            std::atomic_thread_fence(std::memory_order_acquire);
+            return ZMC_OK;
+        }
+        if (now_ms() - t0 > kWatchMs) break;
+    }
+    ZMC_HIP(hipStreamSynchronize(st));
+    ZMC_HIP(hipGetLastError());
+    for (i = 0; i < ns; ++i)
+        if (h_seq_[i] != seq_) {
+            set_error("a level ended without its records");
+            return ZMC_EDEVICE;
+        }
     return ZMC_OK;
 }
 
@@ -482,22 +546,40 @@ int Engine::step(hipStream_t st, const std::vector<LiveSeg>& live, uint64_t* cur
     int32_t* d_flags = (int32_t*)(d_tab_ + flags_offset(ns));
     memset(h_flags, 0, (size_t)ns * sizeof(int32_t));
     size_t up = flags_offset(ns) + (size_t)ns * sizeof(int32_t);
+    const size_t next_off = next_offset(ns);
     if (pend_next_) {
-        const size_t off = next_offset(ns);
-        memcpy(h_tab_ + off, h_nextsegs_, (size_t)pend_n_up_ * sizeof(Segment));
-        up = off + (size_t)pend_n_up_ * sizeof(Segment);
+        memcpy(h_tab_ + next_off, h_nextsegs_, (size_t)pend_n_up_ * sizeof(Segment));
+        up = next_off + (size_t)pend_n_up_ * sizeof(Segment);
     }
-    ZMC_HIP(hipMemcpyAsync(d_tab_, h_tab_, up, hipMemcpyHostToDevice, st));
+    const bool direct = pend_next_ && up <= kDirectTable && (int)pend_slots_.size() <= CopyArgs::kMaxSlots &&
+                        pend_la_.n_tiles <= kFuseMaxTiles;
+    if (!direct) {
+        for (int slot : pend_slots_) {
+            const int rc = upload_slot(slot, st);
+            if (rc != ZMC_OK) return rc;
+        }
+        ZMC_HIP(hipMemcpyAsync(d_tab_, h_tab_, up, hipMemcpyHostToDevice, st));
+    }
     if (pend_next_) {
         // this level's list: children of the last level's selected cubes,
         // then the roots of new integrals
-        Segment* d_next = (Segment*)(d_tab_ + next_offset(ns));
-        if (pend_la_.n_segs > 0) pend_la_.segs = d_next;
-        if (pend_ra_.n_segs > 0) pend_ra_.segs = d_next + pend_n_spawn_segs_;
+        const Segment* next = (const Segment*)((direct ? d_htab_ : d_tab_) + next_off);
+        if (pend_la_.n_segs > 0) pend_la_.segs = next;
+        if (pend_ra_.n_segs > 0) pend_ra_.segs = next + pend_n_spawn_segs_;
+        CopyArgs ca;
+        memset(&ca, 0, sizeof(ca));
+        if (direct) {
+            ca.src = (const uint4*)d_htab_;
+            ca.dst = (uint4*)d_tab_;
+            ca.n = (int32_t)ceil_div((int64_t)flags_offset(ns) + ns * (int64_t)sizeof(int32_t), sizeof(uint4));
+            ca.slot_src = d_hslots_;
+            ca.slot_dst = d_slots_;
+            for (int slot : pend_slots_) ca.slots[ca.n_slots++] = slot;
+        }
         pend_next_ = false;
-        ZMC_HIP(launch_next_list(pend_la_, pend_ra_, st));
+        ZMC_HIP(launch_next_list(pend_la_, pend_ra_, ca, st));
     }
-    ZMC_HIP(hipEventRecord(ev_sample0_, st));
+    pend_slots_.clear();
     int n_launch = 0;
     for (const Launch& L : launches) {
         if (L.units <= 0) continue;
@@ -510,15 +592,21 @@ int Engine::step(hipStream_t st, const std::vector<LiveSeg>& live, uint64_t* cur
         a.uid_hi = cur_hi_;
         a.partial = partial;
         a.seg_flags = d_flags;
+        a.clock = nullptr;
         // one launch, or launches of at most chunk_samples_ samples each
         int64_t chunk = L.units;
         if (chunk_samples_ > 0) chunk = std::max<int64_t>(1, chunk_samples_ / L.unit_samples);
         for (int64_t u0 = 0; u0 < L.units; u0 += chunk) {
             a.unit0 = u0;
+            a.clock = n_launch == 0 ? d_hclock_ : nullptr;
             a.total_units = std::min(chunk, L.units - u0);
             if (L.integrand >= kUserBase) {
                 const int rc = rtc_launch(L.integrand, L.dim, L.eval, st, a);
-                if (rc != ZMC_OK) return rc;
+                if (rc != ZMC_OK) {
+                    // the table's upload may still read the staging memory
+                    (void)hipStreamSynchronize(st);
+                    return rc;
+                }
             } else {
                 const int block = tiles_->block(L.integrand, L.dim, L.eval);
                 const int hint = sums        ? kSumsVariant
@@ -531,7 +619,6 @@ int Engine::step(hipStream_t st, const std::vector<LiveSeg>& live, uint64_t* cur
             ++n_launch;
         }
     }
-    ZMC_HIP(hipEventRecord(ev_sample1_, st));
 
     LevelArgs la;
     memset(&la, 0, sizeof(la));
@@ -555,6 +642,9 @@ int Engine::step(hipStream_t st, const std::vector<LiveSeg>& live, uint64_t* cur
     la.seg_count = d_seg_count_;
     la.host_stats = stats_only ? nullptr : d_hstats_;
     la.seg_flags = d_flags;
+    la.clock = d_hclock_ + 1;
+    la.host_seq = d_hseq_;
+    la.seq = ++seq_;
     // small levels fold the per-segment steps into the tile kernels; a
     // level of one-tile segments without per-parent thresholds runs them all
     // in one launch
@@ -594,11 +684,18 @@ int Engine::step(hipStream_t st, const std::vector<LiveSeg>& live, uint64_t* cur
             }
         }
     }
-    ZMC_HIP(hipStreamSynchronize(st));
-    ZMC_HIP(hipGetLastError());
     last_sample_launches_ = n_launch;
     last_sample_ms_ = 0.0f;
-    ZMC_HIP(hipEventElapsedTime(&last_sample_ms_, ev_sample0_, ev_sample1_));
+    if (stats_only || trace) {
+        // records are not all that is waited for
+        ZMC_HIP(hipStreamSynchronize(st));
+        ZMC_HIP(hipGetLastError());
+    }
+    if (!stats_only) {
+        const int rc = wait_level(st, ns);
+        if (rc != ZMC_OK) return rc;
+        last_sample_ms_ = (float)((double)(h_clock_[1] - h_clock_[0]) * clock_ms_);
+    }
     return ZMC_OK;
 }
 
@@ -690,15 +787,16 @@ int Engine::next_list(hipStream_t st, std::vector<LiveSeg>& live, const std::vec
 
 // ---------------------------------------------------------------------------
 // Shared level loop of run() and serving.
-int Engine::drive(hipStream_t st, Admission& adm, zmc_trace* trace, const std::atomic<bool>* stop_flag,
+int Engine::drive(hipStream_t st, int n_slots, Admission& adm, zmc_trace* trace, const std::atomic<bool>* stop_flag,
                   std::atomic<uint64_t>* levels_stepped)
 {
     std::vector<int> free_ids;
-    for (int i = max_slots_ - 1; i >= 0; --i) free_ids.push_back(i);
+    for (int i = n_slots - 1; i >= 0; --i) free_ids.push_back(i);
     std::vector<LiveSeg> live;
     uint64_t* cur_uid = nullptr;
     cur_hi_ = nullptr;
     pend_next_ = false;
+    pend_slots_.clear();
     int cur_side = 0;
     arena_.reset(0);
     arena_.reset(1);
@@ -743,6 +841,7 @@ int Engine::drive(hipStream_t st, Admission& adm, zmc_trace* trace, const std::a
                 cur_uid = nullptr;
                 cur_hi_ = nullptr;
                 pend_next_ = false;
+                pend_slots_.clear();
                 arena_.reset(0);
                 arena_.reset(1);
                 if (rc == ZMC_EDEVICE) return rc;
@@ -784,8 +883,8 @@ int Engine::drive(hipStream_t st, Admission& adm, zmc_trace* trace, const std::a
             hs.level = 0;
             hs.totM = hs.totS2 = 0.0;
             reserved += hs.reserve;
-            int rc = fill_slot_desc(id, hs.req, st);
-            if (rc != ZMC_OK) return rc;
+            fill_slot_desc(id, hs.req);
+            pend_slots_.push_back(id);
             fresh.push_back({id, (int64_t)ipow_u64((uint64_t)hs.req.divisions_per_axis, hs.req.dim)});
         }
         if (idle && fresh.empty()) {
@@ -818,6 +917,7 @@ int Engine::drive(hipStream_t st, Admission& adm, zmc_trace* trace, const std::a
             cur_uid = nullptr;
             cur_hi_ = nullptr;
             pend_next_ = false;
+            pend_slots_.clear();
             arena_.reset(0);
             arena_.reset(1);
             continue;
@@ -833,7 +933,6 @@ int Engine::run(const zmc_request* reqs, int n, hipStream_t st, zmc_result* outs
         set_error("more requests than slots");
         return ZMC_EINVAL;
     }
-    std::vector<int> id_of_slot(max_slots_, -1);
     int given = 0;
     Admission adm;
     adm.admit = [&](std::vector<HostSlot>& out, int free_slots, size_t, bool, double) {
@@ -862,7 +961,7 @@ int Engine::run(const zmc_request* reqs, int n, hipStream_t st, zmc_result* outs
     };
     adm.cancelled = nullptr;
     const double t0 = now_ms();
-    int rc = drive(st, adm, n == 1 ? trace : nullptr, nullptr, nullptr);
+    int rc = drive(st, n, adm, n == 1 ? trace : nullptr, nullptr, nullptr);
     const double t1 = now_ms();
     for (int i = 0; i < n; ++i) outs[i].latency_ms = t1 - t0;
     return rc;
@@ -880,7 +979,8 @@ int Engine::cube_estimates(const zmc_request& req, int level, const uint64_t* ui
     init_result(hs.res);
     hs.level = level;
     hs.any_arg = any_argument(req);
-    int rc = fill_slot_desc(0, req, st);
+    fill_slot_desc(0, req);
+    int rc = upload_slot(0, st);
     if (rc != ZMC_OK) return rc;
     uint64_t* d_uid = (uint64_t*)arena_.alloc(1, (size_t)n * 8);
     if (!d_uid) return ZMC_ENOMEM;
@@ -919,7 +1019,8 @@ int Engine::debug_points(const zmc_request& req, int level, uint64_t uid, int tr
                          double* x, hipStream_t st)
 {
     arena_.reset(0);
-    int rc = fill_slot_desc(0, req, st);
+    fill_slot_desc(0, req);
+    int rc = upload_slot(0, st);
     if (rc != ZMC_OK) return rc;
     double* dx = (double*)arena_.alloc(0, (size_t)n * req.dim * 8);
     if (!dx) return ZMC_ENOMEM;

@@ -155,8 +155,10 @@ public:
         std::function<void(HostSlot& done)> retire;
         std::function<bool(uint64_t ticket)> cancelled;
     };
-    int drive(hipStream_t st, Admission& adm, zmc_trace* trace, const std::atomic<bool>* stop_flag,
+    // n_slots: slots it may fill (at most max_slots)
+    int drive(hipStream_t st, int n_slots, Admission& adm, zmc_trace* trace, const std::atomic<bool>* stop_flag,
               std::atomic<uint64_t>* levels_stepped);
+    int max_slots() const { return max_slots_; }
 
     size_t reservation_bytes(const zmc_request& r) const;
     size_t budget_bytes() const { return arena_.size(); }
@@ -168,7 +170,9 @@ public:
     int groups_of(const zmc_request& r) const;
 
 private:
-    int fill_slot_desc(int slot, const zmc_request& r, hipStream_t st);
+    void fill_slot_desc(int slot, const zmc_request& r);
+    int upload_slot(int slot, hipStream_t st);
+    int wait_level(hipStream_t st, int ns);
     int step(hipStream_t st, const std::vector<LiveSeg>& live, uint64_t* cur_uid, int cur_side, zmc_trace* trace,
              bool stats_only, bool want_sums);
     int next_list(hipStream_t st, std::vector<LiveSeg>& live, const std::vector<int>& split,
@@ -190,17 +194,25 @@ private:
     size_t tab_bytes_ = 0;
     int32_t* d_seg_count_ = nullptr;
     SegStats* d_hstats_ = nullptr;
+    char* d_htab_ = nullptr;           // h_tab_, h_slots_, h_seq_ and h_clock_ as the device sees them
+    SlotDesc* d_hslots_ = nullptr;
+    uint32_t* d_hseq_ = nullptr;
+    uint64_t* d_hclock_ = nullptr;
+    double clock_ms_ = 1e-5;           // milliseconds a tick of the device clock
     Segment* d_segs_ = nullptr;
     BSeg* d_bsegs_ = nullptr;
     SegStats* d_stats_ = nullptr;
     double2* d_prev_ = nullptr;
     // pinned host staging (each buffer is rewritten only after the stream
-    // has been synchronised past its previous upload)
+    // has passed its previous upload)
     SlotDesc* h_slots_ = nullptr;
     Segment* h_segs_ = nullptr;
     Segment* h_nextsegs_ = nullptr;
     BSeg* h_bsegs_ = nullptr;
     SegStats* h_stats_ = nullptr;
+    volatile uint32_t* h_seq_ = nullptr; // per segment: number of the level h_stats_ holds
+    uint32_t seq_ = 0;
+    volatile uint64_t* h_clock_ = nullptr; // device clock when the level's sampling, its per-cube kernels began
     double2* h_prev_ = nullptr;
     DualStack arena_;
     std::vector<HostSlot> slots_;
@@ -225,8 +237,8 @@ private:
     RootArgs pend_ra_{};
     int pend_n_up_ = 0;
     int pend_n_spawn_segs_ = 0;
+    std::vector<int> pend_slots_; // newly admitted integrals whose descriptors go up with it
     // GPU time of the last level's sampling launches
-    hipEvent_t ev_sample0_ = nullptr, ev_sample1_ = nullptr;
     float last_sample_ms_ = 0.0f;
     int last_sample_launches_ = 0;
 };

@@ -46,6 +46,23 @@ struct LevelArgs {
     int32_t* seg_count;      // per segment: tile blocks done (0 between kernels)
     SegStats* host_stats;    // optional mapped host copy of the decisions
     const int32_t* seg_flags; // per segment: flags the sampling launches raised
+    uint64_t* clock;          // mapped host memory: when the per-cube kernels began (device clock)
+    uint32_t* host_seq;       // per segment, mapped host memory: set to seq once host_stats holds the decision
+    uint32_t seq;             // number of this level, unlike any that came before
+};
+
+// What next_list_kernel copies from mapped host memory into device memory for
+// the kernels that follow it: a small level's table and the descriptors of
+// newly admitted integrals.
+struct CopyArgs {
+    static constexpr int kMaxSlots = 8;
+    const uint4* src; // the table
+    uint4* dst;
+    int32_t n;        // 16-byte words; 0: nothing is copied
+    int32_t n_slots;
+    const SlotDesc* slot_src;
+    SlotDesc* slot_dst;
+    int32_t slots[kMaxSlots];
 };
 
 struct RootArgs {
@@ -82,9 +99,9 @@ hipError_t launch_level_small(const LevelArgs& a, hipStream_t st);
 hipError_t launch_threshold(const LevelArgs& a, hipStream_t st);
 hipError_t launch_group_threshold(const LevelArgs& a, hipStream_t st);
 hipError_t launch_select(const LevelArgs& a, hipStream_t st);
-// Spawn (a.n_tiles blocks, none when 0) and roots (ra.n_segs segments, none
-// when 0) in one launch.
-hipError_t launch_next_list(const LevelArgs& a, const RootArgs& ra, hipStream_t st);
+// Spawn (a.n_tiles blocks, none when 0), roots (ra.n_segs segments, none when
+// 0) and the copies of ca in one launch.
+hipError_t launch_next_list(const LevelArgs& a, const RootArgs& ra, const CopyArgs& ca, hipStream_t st);
 hipError_t launch_debug_philox(uint32_t k0, uint32_t k1, const uint32_t* ctr, uint32_t* out, int64_t n,
                                hipStream_t st);
 hipError_t launch_debug_points(const SlotDesc* sd, int level, uint64_t uid, int trial, int64_t s0, int64_t n,

@@ -330,6 +330,7 @@ __device__ void finalize_tile(const LevelArgs& a, int64_t tile, int si, double* 
 
 __global__ __launch_bounds__(kLevelThreads) void finalize_kernel(const LevelArgs a)
 {
+    if (a.clock && blockIdx.x == 0 && threadIdx.x == 0) *a.clock = device_clock();
     const int64_t tile = blockIdx.x;
     const int si = seg_of_tile(a.segs, a.n_segs, tile);
     const Segment& sg = a.segs[si];
@@ -572,7 +573,8 @@ __device__ void decide_write(const LevelArgs& a, int si, const DecideIn& in, dou
         S.totS2 = totS2;
         if (a.host_stats) {
             a.host_stats[si] = S;
-            __threadfence_system();
+            __threadfence_system(); // the record is in host memory before its number is
+            __hip_atomic_store(a.host_seq + si, a.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         }
     }
 }
@@ -591,6 +593,7 @@ __global__ __launch_bounds__(kLevelThreads) void seg_decide_kernel(const LevelAr
 __global__ __launch_bounds__(kLevelThreads) void level_small_kernel(const LevelArgs a)
 {
     __shared__ double sh[kWaves];
+    if (a.clock && blockIdx.x == 0 && threadIdx.x == 0) *a.clock = device_clock();
     const int si = blockIdx.x;
     const Segment& sg = a.segs[si];
     const int64_t tile = sg.tile_base;
@@ -730,15 +733,26 @@ __device__ void roots_block(const RootArgs& a, int blk)
 }
 
 // The next list in one launch: the first n_spawn blocks spawn children (one
-// per tile of the finished level), the rest write roots of new integrals.
+// per tile of the finished level), the next n_roots write roots of new
+// integrals, and the rest copy a small level's table and the new integrals'
+// descriptors from mapped host memory.
 __global__ __launch_bounds__(kLevelThreads) void next_list_kernel(const LevelArgs a, const RootArgs ra,
-                                                                  int64_t n_spawn)
+                                                                  const CopyArgs ca, int64_t n_spawn, int64_t n_roots)
 {
     const int64_t b = blockIdx.x;
-    if (b < n_spawn)
+    if (b < n_spawn) {
         spawn_tile(a, b);
-    else
+    } else if (b < n_spawn + n_roots) {
         roots_block(ra, (int)(b - n_spawn));
+    } else if (b == n_spawn + n_roots) {
+        for (int i = threadIdx.x; i < ca.n; i += kLevelThreads) ca.dst[i] = ca.src[i];
+    } else {
+        constexpr int kWords = sizeof(SlotDesc) / sizeof(uint4);
+        static_assert(kWords * sizeof(uint4) == sizeof(SlotDesc) && kWords <= kLevelThreads, "one word a thread");
+        const int slot = ca.slots[b - n_spawn - n_roots - 1];
+        if (threadIdx.x < kWords)
+            ((uint4*)(ca.slot_dst + slot))[threadIdx.x] = ((const uint4*)(ca.slot_src + slot))[threadIdx.x];
+    }
 }
 
 // ---- debug entry points ------------------------------------------------------
@@ -814,13 +828,14 @@ hipError_t launch_select(const LevelArgs& a, hipStream_t st)
     return hipGetLastError();
 }
 
-hipError_t launch_next_list(const LevelArgs& a, const RootArgs& ra, hipStream_t st)
+hipError_t launch_next_list(const LevelArgs& a, const RootArgs& ra, const CopyArgs& ca, hipStream_t st)
 {
     const int64_t n_spawn = a.n_tiles > 0 ? a.n_tiles : 0;
     const int64_t n_roots = ra.n_segs > 0 ? (int64_t)ra.n_segs * ra.blocks_per_seg : 0;
-    if (n_spawn + n_roots <= 0) return hipSuccess;
-    hipLaunchKernelGGL(next_list_kernel, dim3((unsigned)(n_spawn + n_roots)), dim3(kLevelThreads), 0, st, a, ra,
-                       n_spawn);
+    const int64_t n_copy = ca.n > 0 ? 1 + ca.n_slots : 0;
+    if (n_spawn + n_roots + n_copy <= 0) return hipSuccess;
+    hipLaunchKernelGGL(next_list_kernel, dim3((unsigned)(n_spawn + n_roots + n_copy)), dim3(kLevelThreads), 0, st, a,
+                       ra, ca, n_spawn, n_roots);
     return hipGetLastError();
 }
 

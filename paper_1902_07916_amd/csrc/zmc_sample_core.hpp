@@ -196,6 +196,7 @@ __device__ __forceinline__ void sample_units(const SampleArgs& a)
     // bookkeeping derived from it) in scalar registers
     const int64_t wave = (int64_t)blockIdx.x * waves_per_block + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t n_waves = (int64_t)gridDim.x * waves_per_block;
+    if (a.clock && wave == 0 && lane == 0) *a.clock = device_clock();
     const int64_t U = a.total_units;
     const int64_t per = (U + n_waves - 1) / n_waves;
     int64_t u = a.unit0 + wave * per;
