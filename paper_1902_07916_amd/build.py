@@ -32,6 +32,17 @@ HIP_FLAGS = [
     "-Wall", "-Wno-unused-command-line-argument",
 ]
 
+# The sampling kernels' own flags.  Loop headers on 64-byte lines: the
+# sampling loop's speed moved by up to 6% with where its header fell in a
+# line.  Scheduling for the fewest registers: each Philox block's chain then
+# runs depth first, dependent instructions one after another, instead of all
+# blocks round by round.  One wave issues a vector instruction every 4-5
+# cycles at best either way (measured), so a chain's latency costs nothing
+# beside other waves.  Same source, points/s: 6-D sine FP32 5.40e11 -> 5.75e11,
+# 6-D Genz Gaussian 5.25e11 -> 5.60e11, 12-D corner peak 2.77e11 -> 2.86e11;
+# VGPRs at 6, 9 and 12-D: 73 -> 60, 132 -> 96, 134 -> 104.
+SAMPLE_FLAGS = ["-falign-loops=64", "-mllvm", "-amdgpu-sched-strategy=iterative-minreg"]
+
 
 def hipcc() -> str:
     for cand in (shutil.which("hipcc"), "/opt/rocm/bin/hipcc"):
@@ -81,10 +92,8 @@ def write_rtc_embed() -> str:
 def _units():
     units = []
     for f in range(N_INTEGRANDS):
-        # loop headers on 64-byte lines: the sampling loop's speed moved by
-        # up to 6% with where its header fell in a line
         units.append((os.path.join(CSRC, "zmc_sample.hip"), os.path.join(BUILD, f"zmc_sample_{f}.o"),
-                      [f"-DZMC_F={f}", "-falign-loops=64"]))
+                      [f"-DZMC_F={f}"] + SAMPLE_FLAGS))
     # the per-cube / per-integral kernels round every product and sum
     # separately, in the order the method states them (no FMA contraction)
     units.append((os.path.join(CSRC, "zmc_level.hip"), os.path.join(BUILD, "zmc_level.o"), ["-ffp-contract=off"]))
@@ -114,13 +123,13 @@ def _compile(src, obj, extra, skip_if_newer=None):
 
 
 TUNE_DEFAULT = os.path.join(CSRC, "zmc_tune_gfx950.json")
-WAVE_HINTS = (1, 5, 7, 8)  # must match kWaveHints in zmc_kernels.hpp
+WAVE_HINTS = (1, 4, 5, 6)  # must match kWaveHints in zmc_kernels.hpp
 
 
 def write_tune_default() -> str:
     """_build/zmc_tune_default.inc: the built-in occupancy variant and block
     shape per (integrand, dim, eval), from the measured table
-    zmc_tune_gfx950.json (keys "integrand:dim:eval:w" -> minimum waves per
+    zmc_tune_gfx950.json (keys "integrand:dim:eval:w" -> waves per
     SIMD, absent = 1; "integrand:dim:eval:b" -> threads per block, absent =
     256)."""
     table = json.load(open(TUNE_DEFAULT)) if os.path.exists(TUNE_DEFAULT) else {}

@@ -147,8 +147,9 @@ TileTable::TileTable()
 
 // Tuning file: a JSON object whose keys "integrand:dim:eval" map to the
 // number of 4-point groups per thread per chunk, e.g. {"1:6:1": 8}, whose
-// keys "integrand:dim:eval:w" map to the minimum waves per SIMD of the
-// occupancy variant (one of kWaveHints), e.g. {"1:6:1:w": 8}, and whose keys
+// keys "integrand:dim:eval:w" map to the waves per SIMD of the
+// occupancy variant (one of kWaveHints; 7 and 8, variants of earlier tuning
+// files, take the one of 6), e.g. {"1:6:1:w": 5}, and whose keys
 // "integrand:dim:eval:b" map to the threads per sampling block (64, 128 or
 // 256), e.g. {"1:6:1:b": 128}.
 int TileTable::load(const char* path)
@@ -175,7 +176,7 @@ int TileTable::load(const char* path)
         if (nf == 3 && g >= 1 && g <= 64) groups[f][d][e] = g;
         if (nf == 4 && w == 'w')
             for (int h = 0; h < kNumWaveHints; ++h)
-                if (kWaveHints[h] == g) hint[f][d][e] = h;
+                if (kWaveHints[h] == (g == 7 || g == 8 ? 6 : g)) hint[f][d][e] = h;
         if (nf == 4 && w == 'b' && valid_block(g)) threads[f][d][e] = g;
     }
     return 0;

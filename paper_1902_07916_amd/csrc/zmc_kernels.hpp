@@ -74,11 +74,11 @@ struct RootArgs {
 };
 
 // Launchers; each returns the hipError_t of its launch.
-// Occupancy variants of every sampling kernel: the minimum waves per SIMD
-// the register allocator must allow (1 = no constraint).  More resident waves
-// hide more of the Philox latency, until the registers they leave each wave
-// make the allocator spill; which variant wins depends on the bucket.
-constexpr int kWaveHints[] = {1, 5, 7, 8};
+// Occupancy variants of every sampling kernel: the waves per SIMD the
+// register allocator and the scheduler aim at (1 = no constraint).  Most
+// buckets run within 2% of their best in the first; where more registers or
+// more waves pay, which variant wins depends on the bucket and is measured.
+constexpr int kWaveHints[] = {1, 4, 5, 6};
 constexpr int kNumWaveHints = 4;
 // hint value that selects the sampling kernel that also keeps the sums of
 // squares (traced levels); it runs at the compiler's default occupancy

@@ -15,10 +15,10 @@ namespace zmc {
 namespace {
 
 template <int F, int D, bool FP32, int W>
-__global__ __launch_bounds__(kSampleThreads) __attribute__((amdgpu_waves_per_eu(W))) void sample_kernel(
-    const SampleArgs a)
+__global__ __launch_bounds__(kSampleThreads) __attribute__((amdgpu_waves_per_eu(W, W == 1 ? 8 : W))) void
+sample_kernel(const SampleArgs a)
 {
-    sample_units<Integrand<F, D>, D, FP32, false, W>(a);
+    sample_units<Integrand<F, D>, D, FP32, false>(a);
 }
 
 // the variant that also keeps the sums of squares, for traced levels

@@ -98,49 +98,24 @@ __device__ __forceinline__ void corner(const SlotDesc& sd, int level, uint64_t u
 }
 
 // The 4 samples of a thread's group take words s*D + i, s = 0..3, i < D:
-// Philox blocks cb .. cb + D - 1 (4 words each).  Blocks are generated in
-// lockstep (independent chains for the issue pipeline).  For D >= kHalvesMinD
-// they are generated in two halves, the blocks holding samples 0-1 and then
-// the rest, and each half's samples are evaluated before the next half is
-// generated: the words live at once halve, which leaves registers for more
-// waves.  eval(q, w) gets sample q's D words in order.
-constexpr int kHalvesMinD = 10;
-
+// Philox blocks cb .. cb + D - 1 (4 words each), generated in lockstep in the
+// source; the scheduler orders them by register need (see build.py).
+// eval(q, w) gets sample q's D words in order.
 template <int D, class Eval>
 __device__ __forceinline__ void group_samples(uint32_t cb, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0,
                                               uint32_t k1, Eval&& eval)
 {
-    constexpr int HA = D >= kHalvesMinD ? (D + 1) / 2 : D; // blocks of the first half
-    constexpr int HB = D - HA;
-    uint32_t ca[HA];
-    uint32_t wa[4 * HA];
+    uint32_t c[D];
+    uint32_t w[4 * D];
 #pragma unroll
-    for (int k = 0; k < HA; ++k) ca[k] = cb + (uint32_t)k;
-    philox4x32_10_lockstep<HA>(ca, c1, c2, c3, k0, k1, wa);
-    constexpr int QA = HB > 0 ? 2 : 4; // samples wholly inside the first half
+    for (int k = 0; k < D; ++k) c[k] = cb + (uint32_t)k;
+    philox4x32_10_lockstep<D>(c, c1, c2, c3, k0, k1, w);
 #pragma unroll
-    for (int q = 0; q < QA; ++q) {
+    for (int q = 0; q < 4; ++q) {
         uint32_t ws[D];
 #pragma unroll
-        for (int i = 0; i < D; ++i) ws[i] = wa[q * D + i];
+        for (int i = 0; i < D; ++i) ws[i] = w[q * D + i];
         eval(q, ws);
-    }
-    if constexpr (HB > 0) {
-        uint32_t cbk[HB];
-        uint32_t wb[4 * HB];
-#pragma unroll
-        for (int k = 0; k < HB; ++k) cbk[k] = cb + (uint32_t)(HA + k);
-        philox4x32_10_lockstep<HB>(cbk, c1, c2, c3, k0, k1, wb);
-#pragma unroll
-        for (int q = 2; q < 4; ++q) {
-            uint32_t ws[D];
-#pragma unroll
-            for (int i = 0; i < D; ++i) {
-                const int n = q * D + i; // words 2D .. 4HA - 1 are left from the first half
-                ws[i] = n < 4 * HA ? wa[n] : wb[n - 4 * HA];
-            }
-            eval(q, ws);
-        }
     }
 }
 
@@ -184,9 +159,7 @@ struct CubeState<I, D, false> {
 // KEEP_S2: also accumulate the sum of squares (only the per-(cube, trial)
 // trace reads it; the estimator uses the sums alone).  Without it the
 // partial's second member is 0.
-// W: the occupancy variant's minimum waves per SIMD (1 = unconstrained); it
-// decides whether whole and ragged groups get loops of their own (below).
-template <class I, int D, bool FP32, bool KEEP_S2, int W = 1>
+template <class I, int D, bool FP32, bool KEEP_S2>
 __device__ __forceinline__ void sample_units(const SampleArgs& a)
 {
     // blocks of 64, 128 or 256 threads (the tile table's block shape)
@@ -258,9 +231,15 @@ __device__ __forceinline__ void sample_units(const SampleArgs& a)
         const uint32_t k0 = (uint32_t)sd->seed, k1 = (uint32_t)(sd->seed >> 32);
         const uint32_t c1 = ctr_word1(trial, level, uid_hi);
         const uint32_t c2 = (uint32_t)uid, c3 = (uint32_t)(uid >> 32);
-        const int64_t N = sd->samples;
-        const int G = sd->groups;
-        const int64_t g0 = (int64_t)chunk * G * 64 + lane;
+        // This chunk's points: whole groups of all 64 lanes, then at most one
+        // group in which lanes stop short.  The counts are wave-uniform and
+        // kept in scalar registers (the loads they come from are vector
+        // loads), so that the loop's control takes no vector instruction.
+        const int G = __builtin_amdgcn_readfirstlane(sd->groups);
+        const int64_t left = sd->samples - (int64_t)chunk * G * 256;
+        const int pts = __builtin_amdgcn_readfirstlane((int)min((int64_t)G * 256, left));
+        const int n_whole = pts >> 8;
+        uint32_t cb = (uint32_t)((int64_t)chunk * G * 64 + lane) * (uint32_t)D; // the lane's next Philox block
 
         double S1 = 0.0, S2 = 0.0;
         // FP64 evaluation: the cell bits of a word and its mid-cell bit, in
@@ -268,97 +247,66 @@ __device__ __forceinline__ void sample_units(const SampleArgs& a)
         // half the rate of the same one without)
         [[maybe_unused]] uint32_t cell_mask = 0xFFFFFE00u, cell_mid = 0x100u;
         if constexpr (!FP32) asm("" : "+v"(cell_mask), "+v"(cell_mid));
-        // Groups of 4 points; with N a multiple of 4 every group a lane
-        // reaches is whole, otherwise the group holding point N - 1 is cut
-        // short and its points past N count as 0.  Where registers allow,
-        // the two cases are separate loops, so that whole groups carry no
-        // per-point mask (1-3% faster).  The second loop costs registers: in
-        // the 7- and 8-wave variants from D = 7 (8-wave: from D = 5) it made
-        // the allocator spill (up to 66% slower), and from D = kHalvesMinD
-        // on the mask costs under 1%; those keep the one masked loop.
-        // In FP32 evaluation up to D = 3, a chunk holding G * 256 points or
-        // more (every lane has G whole groups) also drops the per-lane exit
-        // test: a wave-uniform trip count.  From D = 4 on, and in FP64, that
-        // loop took more registers than it saved instructions (one wave per
-        // SIMD less in several buckets).
-        // FP32 evaluation adds a group's 4 values in FP32 and the group's sum
-        // in FP64: one conversion and one FP64 add per group instead of per
-        // point.  The 4 values are added in point order, except at D = 6 and
-        // 7, where (v0 + v1) + (v2 + v3) ran 1-2.4% faster than both the
-        // point-order sum and per-value FP64 adds in a same-box A/B (and
-        // 0.5-3.7% slower at the other D).
-        constexpr bool kWholeLoop = D < kHalvesMinD && (W <= 5 || (W == 7 && D <= 6));
-        constexpr bool kUniformLoop = FP32 && D <= 3;
+        // Groups of 4 points.  FP32 evaluation adds a group's 4 values in
+        // FP32 and the group's sum in FP64: one conversion and one FP64 add
+        // per group instead of per point.  The 4 values are added in point
+        // order, except at D = 6 and 7, where (v0 + v1) + (v2 + v3) ran
+        // 1-2.4% faster than both the point-order sum and per-value FP64 adds
+        // in a same-box A/B (and 0.5-3.7% slower at the other D).
         constexpr bool kPairSum = D == 6 || D == 7;
-        auto run = [&](auto masked, auto tested) {
-            constexpr bool kMasked = decltype(masked)::value;
-            for (int j = 0; j < G; ++j) {
-                const int64_t g = g0 + (int64_t)j * 64;
-                int nvalid = 4;
-                if constexpr (decltype(tested)::value) {
-                    const int64_t s0 = 4 * g;
-                    if (s0 >= N) break;
-                    if constexpr (kMasked) nvalid = (int)min((int64_t)4, N - s0);
-                }
-                [[maybe_unused]] float gs = 0.0f, gb = 0.0f;
-                group_samples<D>((uint32_t)g * (uint32_t)D, c1, c2, c3, k0, k1, [&](int q, const uint32_t* w) {
-                    if constexpr (FP32) {
-                        float v[D];
+        // nvalid: the lane's points of a ragged group that count
+        auto group = [&](auto ragged, int nvalid) {
+            constexpr bool kRagged = decltype(ragged)::value;
+            [[maybe_unused]] float gs = 0.0f, gb = 0.0f;
+            group_samples<D>(cb, c1, c2, c3, k0, k1, [&](int q, const uint32_t* w) {
+                if constexpr (FP32) {
+                    float v[D];
 #pragma unroll
-                        for (int i = 0; i < D; ++i) v[i] = unit_interval_f32(w[i]);
-                        float f = I::f32(cs.p, v);
-                        if constexpr (kMasked) f = (q < nvalid) ? f : 0.0f;
-                        if constexpr (kPairSum) {
-                            if (q == 0) gs = f;
-                            else if (q == 1) gs = gs + f;
-                            else if (q == 2) gb = f;
-                            else gb = gb + f;
-                        } else {
-                            gs = q == 0 ? f : gs + f;
-                        }
-                        if constexpr (KEEP_S2) {
-                            const double fd = (double)f;
-                            S2 = fma(fd, fd, S2);
-                        }
+                    for (int i = 0; i < D; ++i) v[i] = unit_interval_f32(w[i]);
+                    float f = I::f32(cs.p, v);
+                    if constexpr (kRagged) f = (q < nvalid) ? f : 0.0f;
+                    if constexpr (kPairSum) {
+                        if (q == 0) gs = f;
+                        else if (q == 1) gs = gs + f;
+                        else if (q == 2) gb = f;
+                        else gb = gb + f;
                     } else {
-                        double x[D];
-                        // x = fma(h, (2*(w>>9)+1) 2^-24, lo) computed as
-                        // fma(h 2^-32, (w & ~511) | 256, lo): the same exact
-                        // product, the word placed by one three-input
-                        // instruction instead of a shift and an OR (FP64
-                        // evaluation is bound by VALU issue: 3.6-5% faster,
-                        // the 6-D sine over 6^6 cubes of 16384 points 2.56e11
-                        // -> 2.66e11 points/s, the 9-D Gaussian 2.22e11 ->
-                        // 2.34e11)
-#pragma unroll
-                        for (int i = 0; i < D; ++i)
-                            x[i] = fma(cs.h32[i], (double)bits_or(w[i], cell_mask, cell_mid), cs.lo[i]);
-                        double f = I::f64(cs.p, x);
-                        if constexpr (kMasked) f = (q < nvalid) ? f : 0.0;
-                        S1 += f;
-                        if constexpr (KEEP_S2) S2 = fma(f, f, S2);
+                        gs = q == 0 ? f : gs + f;
                     }
-                });
-                if constexpr (FP32) S1 += (double)(kPairSum ? gs + gb : gs);
-            }
+                    if constexpr (KEEP_S2) {
+                        const double fd = (double)f;
+                        S2 = fma(fd, fd, S2);
+                    }
+                } else {
+                    double x[D];
+                    // x = fma(h, (2*(w>>9)+1) 2^-24, lo) computed as
+                    // fma(h 2^-32, (w & ~511) | 256, lo): the same exact
+                    // product, the word placed by one three-input
+                    // instruction instead of a shift and an OR (FP64
+                    // evaluation is bound by VALU issue: 3.6-5% faster,
+                    // the 6-D sine over 6^6 cubes of 16384 points 2.56e11
+                    // -> 2.66e11 points/s, the 9-D Gaussian 2.22e11 ->
+                    // 2.34e11)
+#pragma unroll
+                    for (int i = 0; i < D; ++i)
+                        x[i] = fma(cs.h32[i], (double)bits_or(w[i], cell_mask, cell_mid), cs.lo[i]);
+                    double f = I::f64(cs.p, x);
+                    if constexpr (kRagged) f = (q < nvalid) ? f : 0.0;
+                    S1 += f;
+                    if constexpr (KEEP_S2) S2 = fma(f, f, S2);
+                }
+            });
+            if constexpr (FP32) S1 += (double)(kPairSum ? gs + gb : gs);
+            cb += 64u * (uint32_t)D;
         };
-        if constexpr (kWholeLoop && kUniformLoop) {
-            const int64_t left = N - (int64_t)chunk * G * 256; // this chunk's points onward (wave-uniform)
-            if (left >= (int64_t)G * 256) run(BoolTag<false>{}, BoolTag<false>{});
-            else run(BoolTag<true>{}, BoolTag<true>{});
-        } else if constexpr (kWholeLoop) {
-            if ((N & 3) == 0) run(BoolTag<false>{}, BoolTag<true>{});
-            else run(BoolTag<true>{}, BoolTag<true>{});
-        } else {
-            run(BoolTag<true>{}, BoolTag<true>{});
-        }
+        for (int j = 0; j < n_whole; ++j) group(BoolTag<false>{}, 4);
+        if (pts & 255) group(BoolTag<true>{}, (pts & 255) - 4 * lane);
 
         S1 = wave_sum(S1);
         if constexpr (KEEP_S2) S2 = wave_sum(S2);
         if constexpr (FP32) {
             if constexpr (I::kRangeCheck) {
                 // values below FP32's normal range: report it for the segment
-                const int64_t pts = min((int64_t)G * 256, N - (int64_t)chunk * G * 256);
                 if (lane == 0 && fabs(S1) < (double)pts * 0x1p-126)
                     atomicOr(a.seg_flags + a.bsegs[bs].seg, kRangeLost);
             }

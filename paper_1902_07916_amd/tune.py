@@ -74,7 +74,7 @@ def time_bucket(name: str, D: int, eval_: str, groups: int, n_cubes: int = 4096,
 
 
 REGISTRY = ("sin_sum", "gauss", "genz_osc", "genz_ppeak", "genz_cpeak", "genz_gauss")
-WAVE_HINTS = (1, 5, 7, 8)  # the library's occupancy variants (minimum waves per SIMD)
+WAVE_HINTS = (1, 4, 5, 6)  # the library's occupancy variants (waves per SIMD)
 MIN_GAIN = 1.015        # a variant must beat the unconstrained kernel by 1.5% to be chosen
 # Seconds of back-to-back runs of a bucket's level before it is timed: the
 # GPU clock rises over the first tens of milliseconds of load, and a short
