@@ -602,7 +602,7 @@ int Engine::step(hipStream_t st, const std::vector<LiveSeg>& live, uint64_t* cur
             a.clock = n_launch == 0 ? d_hclock_ : nullptr;
             a.total_units = std::min(chunk, L.units - u0);
             if (L.integrand >= kUserBase) {
-                const int rc = rtc_launch(L.integrand, L.dim, L.eval, st, a);
+                const int rc = rtc_launch(L.integrand, L.dim, L.eval, sums, st, a);
                 if (rc != ZMC_OK) {
                     // the table's upload may still read the staging memory
                     (void)hipStreamSynchronize(st);

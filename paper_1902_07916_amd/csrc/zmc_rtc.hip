@@ -10,7 +10,10 @@
 // using x[0..D-1] (the point, `real` is double or float), p[0..n_params-1]
 // (the request's params) and D.  The body is compiled once per (D, eval) on
 // first use, around the same sampling body as the precompiled registry
-// (zmc_sample_core.hpp); the device headers are embedded in the library at
+// (zmc_sample_core.hpp), and once more with the sums of squares kept if a level
+// is traced (a conversion and an FP64 FMA per point: bodies of 3 to 9
+// dimensions ran 2-8% faster without, a 6- and a 9-D FP32 Gaussian 2% slower);
+// the device headers are embedded in the library at
 // build time, so nothing is read from disk at run time.
 #include <hip/hip_runtime.h>
 #include <hip/hiprtc.h>
@@ -42,7 +45,7 @@ struct Compiled {
 
 std::mutex g_mu;
 std::vector<UserDef> g_defs;
-std::map<std::tuple<int, int, int>, Compiled> g_cache;
+std::map<std::tuple<int, int, int, bool>, Compiled> g_cache; // (id, D, eval, sums of squares kept)
 
 const char* kPrelude = R"ZMCRTC(
 typedef __hip_internal::uint64_t uint64_t;
@@ -52,11 +55,16 @@ typedef __hip_internal::int32_t int32_t;
 typedef __hip_internal::uint8_t uint8_t;
 )ZMCRTC";
 
-std::string program_source(const std::string& body, int dim, bool fp32)
+std::string program_source(const std::string& body, int dim, bool fp32, bool keep_s2)
 {
     std::string s = kPrelude;
     s += "#define ZMC_D " + std::to_string(dim) + "\n";
     s += "#define ZMC_FP32 " + std::string(fp32 ? "true" : "false") + "\n";
+    // four waves per SIMD where many FP32 words are live (9-D Gaussian body
+    // 2.85e11 -> 2.89e11 points/s); fewer registers than that leave none for
+    // a larger body, and at D = 3 the bound costs 4%
+    s += "#define ZMC_OCCUPANCY " + std::string(fp32 && dim >= 8 ? "__attribute__((amdgpu_waves_per_eu(4)))" : "") + "\n";
+    s += "#define ZMC_KEEP_S2 " + std::string(keep_s2 ? "true" : "false") + "\n";
     s += R"ZMCRTC(
 #include "zmc_sample_core.hpp"
 #include "zmc_trig.hpp"
@@ -123,9 +131,9 @@ struct UserIntegrand {
     }
 };
 } // namespace zmc
-extern "C" __global__ __launch_bounds__(256) void zmc_user_kernel(const zmc::SampleArgs a)
+extern "C" __global__ __launch_bounds__(256) ZMC_OCCUPANCY void zmc_user_kernel(const zmc::SampleArgs a)
 {
-    zmc::sample_units<zmc::UserIntegrand<ZMC_D>, ZMC_D, ZMC_FP32, true>(a);
+    zmc::sample_units<zmc::UserIntegrand<ZMC_D>, ZMC_D, ZMC_FP32, ZMC_KEEP_S2>(a);
 }
 )ZMCRTC";
     return s;
@@ -133,19 +141,21 @@ extern "C" __global__ __launch_bounds__(256) void zmc_user_kernel(const zmc::Sam
 
 // Compile one variant to a code object; returns 0 and fills `code`, or -1
 // with the compiler log in `log`.
-int compile(const std::string& body, int dim, bool fp32, std::vector<char>& code, std::string& log)
+int compile(const std::string& body, int dim, bool fp32, bool keep_s2, std::vector<char>& code, std::string& log)
 {
-    const std::string src = program_source(body, dim, fp32);
+    const std::string src = program_source(body, dim, fp32, keep_s2);
     hiprtcProgram prog;
     if (hiprtcCreateProgram(&prog, src.c_str(), "zmc_user.hip", kRtcHeaderCount, kRtcHeaderSources,
                             kRtcHeaderNames) != HIPRTC_SUCCESS) {
         log = "hiprtcCreateProgram failed";
         return -1;
     }
-    // no packed FP32 instructions (v_pk_*_f32), as in the precompiled kernels
+    // no packed FP32 instructions (v_pk_*_f32) and aligned loop headers, as in
+    // the precompiled kernels (not their scheduling strategy, which has been
+    // seen through on known integrands only)
     const char* opts[] = {"--gpu-architecture=gfx950", "-O3", "-std=c++17",
-                          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"};
-    const hiprtcResult rc = hiprtcCompileProgram(prog, 7, opts);
+                          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-falign-loops=64"};
+    const hiprtcResult rc = hiprtcCompileProgram(prog, (int)(sizeof(opts) / sizeof(opts[0])), opts);
     size_t ls = 0;
     hiprtcGetProgramLogSize(prog, &ls);
     if (ls > 1) {
@@ -177,7 +187,7 @@ int rtc_register(const char* body, int n_params, int* id)
     // compile once (D = 4, FP64) so that syntax errors surface now
     std::vector<char> code;
     std::string log;
-    if (compile(body, 4, false, code, log) != 0) {
+    if (compile(body, 4, false, false, code, log) != 0) {
         set_error("user integrand does not compile:\n" + log);
         return ZMC_EINVAL;
     }
@@ -202,9 +212,9 @@ int rtc_n_params(int id)
 // The kernel for (id, D, eval) on the current device, compiled on first use.
 // The compiler runs outside the lock, so launches of kernels already built
 // never wait behind a compilation.
-static int rtc_get(int id, int dim, int eval, Compiled& out)
+static int rtc_get(int id, int dim, int eval, bool keep_s2, Compiled& out)
 {
-    const auto key = std::make_tuple(id, dim, eval);
+    const auto key = std::make_tuple(id, dim, eval, keep_s2);
     std::string body;
     {
         std::lock_guard<std::mutex> lk(g_mu);
@@ -222,7 +232,7 @@ static int rtc_get(int id, int dim, int eval, Compiled& out)
     }
     std::vector<char> code;
     std::string log;
-    if (compile(body, dim, eval == ZMC_EVAL_FP32, code, log) != 0) {
+    if (compile(body, dim, eval == ZMC_EVAL_FP32, keep_s2, code, log) != 0) {
         set_error("user integrand does not compile:\n" + log);
         return ZMC_EINVAL;
     }
@@ -250,10 +260,10 @@ static int rtc_get(int id, int dim, int eval, Compiled& out)
     return ZMC_OK;
 }
 
-int rtc_launch(int id, int dim, int eval, hipStream_t st, const SampleArgs& a)
+int rtc_launch(int id, int dim, int eval, bool keep_s2, hipStream_t st, const SampleArgs& a)
 {
     Compiled c;
-    const int rc = rtc_get(id, dim, eval, c);
+    const int rc = rtc_get(id, dim, eval, keep_s2, c);
     if (rc != ZMC_OK) return rc;
     const unsigned grid = (unsigned)std::min<int64_t>(a.total_units, c.capacity);
     SampleArgs arg = a;

@@ -17,6 +17,6 @@ int rtc_register(const char* body, int n_params, int* id);
 int rtc_n_params(int id);
 // Launch the (id, dim, eval) sampling kernel (compiled on first use) over
 // the a.total_units units from a.unit0 on, with a persistent grid.
-int rtc_launch(int id, int dim, int eval, hipStream_t st, const SampleArgs& a);
+int rtc_launch(int id, int dim, int eval, bool keep_s2, hipStream_t st, const SampleArgs& a);
 
 } // namespace zmc

@@ -77,3 +77,23 @@ def test_user_body_gives_the_same(z, case, body):
     a = z.integrate(**w)
     b = z.integrate(**dict(w, integrand=uid))
     assert (a.integral, a.std, a.cubes_per_level) == (b.integral, b.std, b.cubes_per_level)
+
+
+@pytest.mark.parametrize("dim,eval_", [(2, "fp32"), (7, "fp32"), (8, "fp32"), (12, "fp32"), (9, "fp64")])
+def test_user_kernel_traced_and_not(z, orc, dim, eval_):
+    """A user body's kernel without the sums of squares (untraced levels)
+    gives the sums of the one that keeps them, which match the oracle's."""
+    import paper_1902_07916_amd as pkg
+    from common import FP32_TRIAL_TOL, U64
+    body = "real t = 1; for (int i = 0; i < D; ++i) t += (real)p[0] * x[i]; return 1 / t;"
+    uid = pkg.register_integrand(body, 1)
+    orc.set_user(uid, body, 1)
+    w = dict(integrand=uid, params=[0.7], lower=[0.0] * dim, upper=[1.0] * dim, divisions=2 if dim < 12 else 1,
+             samples=1027, trials=3, max_depth=0, sigma_mult=1.0, seed=5, eval=eval_)
+    plain = z.integrate(**w)
+    r = z.integrate(**w, trace=True, trace_capacity=1 << 10)
+    assert (plain.integral, plain.std) == (r.integral, r.std)
+    o = orc.integrate(oracle_problem(orc, w))
+    # FP64: two summation orders of 1027 values, each of D + 3 roundings
+    tol = FP32_TRIAL_TOL if eval_ == "fp32" else (2 * 1027 + 2 * (dim + 3)) * U64
+    assert abs(r.integral - o.integral) <= tol * abs(o.integral)
