@@ -54,6 +54,10 @@ constexpr int64_t kFuseMaxTiles = 256;
 // two events around the sampling and a stream synchronisation.
 constexpr size_t kDirectTable = 4096;
 
+// The most children the one-block level of a single integral lays out itself:
+// one block writes them, 32 a thread at most.
+constexpr int64_t kAheadMax = 16384;
+
 // The host watches for a level's records in mapped memory this long before it
 // blocks in the runtime.  Watching sees a short level's end 4-5 us sooner; a
 // level that takes longer loses nothing by the wait.
@@ -442,6 +446,8 @@ int Engine::step(hipStream_t st, const std::vector<LiveSeg>& live, uint64_t* cur
                  zmc_trace* trace, bool stats_only, bool want_sums)
 {
     const int ns = (int)live.size();
+    const bool ready = table_ready_;
+    table_ready_ = false;
     int64_t cube = 0, part = 0, tile = 0, groups = 0;
     bool any_thr = false;
     h_prev_ = (double2*)(h_tab_ + prev_offset(ns));
@@ -554,7 +560,7 @@ int Engine::step(hipStream_t st, const std::vector<LiveSeg>& live, uint64_t* cur
     }
     const bool direct = pend_next_ && up <= kDirectTable && (int)pend_slots_.size() <= CopyArgs::kMaxSlots &&
                         pend_la_.n_tiles <= kFuseMaxTiles;
-    if (!direct) {
+    if (!direct && !ready) {
         for (int slot : pend_slots_) {
             const int rc = upload_slot(slot, st);
             if (rc != ZMC_OK) return rc;
@@ -646,6 +652,30 @@ int Engine::step(hipStream_t st, const std::vector<LiveSeg>& live, uint64_t* cur
     la.clock = d_hclock_ + 1;
     la.host_seq = d_hseq_;
     la.seq = ++seq_;
+    ahead_uid_ = nullptr;
+    ahead_hi_ = nullptr;
+    if (!stats_only && !trace && ns == 1 && tile == 1 && h_segs_[0].need_thr && groups == 0) {
+        // room for the children of every cube that Cantelli's inequality lets
+        // exceed the threshold (in exact arithmetic: the kernel and
+        // next_list() check the count against the room)
+        const HostSlot& hs = slots_[live[0].slot];
+        const double sm = hs.req.sigma_mult;
+        const int64_t most = sm > 0.0 ? (int64_t)((double)cube / (1.0 + sm * sm)) + 1 : cube;
+        const int64_t n = most * kids_of(hs.req);
+        if (n <= kAheadMax) {
+            uint64_t* u = (uint64_t*)arena_.alloc(cur_side ^ 1, (size_t)n * sizeof(uint64_t));
+            uint32_t* h = u && hs.wide ? (uint32_t*)arena_.alloc(cur_side ^ 1, (size_t)n * sizeof(uint32_t)) : nullptr;
+            if (u && (h || !hs.wide)) {
+                la.ahead_uid = ahead_uid_ = u;
+                la.ahead_cap = ahead_cap_ = n;
+                la.ahead_uid_hi = ahead_hi_ = h;
+                la.ahead_seg = d_segs_;
+                la.ahead_bseg = d_bsegs_;
+                la.ahead_prev = d_prev_;
+                la.ahead_flags = d_flags;
+            }
+        }
+    }
     // small levels fold the per-segment steps into the tile kernels; a
     // level of one-tile segments without per-parent thresholds runs them all
     // in one launch
@@ -709,6 +739,25 @@ int Engine::next_list(hipStream_t st, std::vector<LiveSeg>& live, const std::vec
     std::vector<LiveSeg> nxt;
     int64_t total = 0;
     const int ns = (int)live.size();
+    const int other = cur_side ^ 1;
+    if (ahead_uid_ && ns == 1 && split[0] && fresh.empty() &&
+        h_stats_[0].n_sel * kids_of(slots_[live[0].slot].req) <= ahead_cap_) {
+        // the level kernel wrote this list and its table
+        HostSlot& hs = slots_[live[0].slot];
+        live[0].n_cubes = h_stats_[0].n_sel * kids_of(hs.req);
+        hs.level += 1;
+        arena_.reset(cur_side);
+        cur_side = other;
+        cur_uid = ahead_uid_;
+        cur_hi_ = ahead_hi_;
+        ahead_uid_ = nullptr;
+        table_ready_ = true;
+        return ZMC_OK;
+    }
+    if (ahead_uid_) {
+        arena_.reset(other); // not needed: new integrals join, or the integral ended
+        ahead_uid_ = nullptr;
+    }
     bool any_split = false;
     for (int i = 0; i < ns; ++i) any_split |= split[i] != 0;
     const int n_spawn_segs = any_split ? ns : 0;
@@ -736,7 +785,6 @@ int Engine::next_list(hipStream_t st, std::vector<LiveSeg>& live, const std::vec
         total += fresh[j].n_cubes;
         nxt.push_back(fresh[j]);
     }
-    const int other = cur_side ^ 1;
     uint64_t* next_uid = nullptr;
     uint32_t* next_hi = nullptr;
     bool wide = false;
@@ -798,6 +846,8 @@ int Engine::drive(hipStream_t st, int n_slots, Admission& adm, zmc_trace* trace,
     cur_hi_ = nullptr;
     pend_next_ = false;
     pend_slots_.clear();
+    ahead_uid_ = nullptr;
+    table_ready_ = false;
     int cur_side = 0;
     arena_.reset(0);
     arena_.reset(1);
@@ -987,6 +1037,8 @@ int Engine::cube_estimates(const zmc_request& req, int level, const uint64_t* ui
     if (!d_uid) return ZMC_ENOMEM;
     cur_hi_ = nullptr; // ids given here are below 2^64
     pend_next_ = false;
+    ahead_uid_ = nullptr;
+    table_ready_ = false;
     ZMC_HIP(hipMemcpyAsync(d_uid, uids, (size_t)n * 8, hipMemcpyHostToDevice, st));
     std::vector<LiveSeg> live{{0, n}};
     rc = step(st, live, d_uid, 0, nullptr, true, S1 != nullptr || S2 != nullptr);

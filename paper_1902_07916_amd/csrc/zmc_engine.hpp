@@ -237,6 +237,11 @@ private:
     RootArgs pend_ra_{};
     int pend_n_up_ = 0;
     int pend_n_spawn_segs_ = 0;
+    // the next list laid out ahead by the level kernel (LevelArgs::ahead_uid)
+    uint64_t* ahead_uid_ = nullptr; // of the level last stepped, NULL if it was not
+    uint32_t* ahead_hi_ = nullptr;
+    int64_t ahead_cap_ = 0;         // children it holds
+    bool table_ready_ = false;      // the device holds the next level's list and table
     std::vector<int> pend_slots_; // newly admitted integrals whose descriptors go up with it
     // GPU time of the last level's sampling launches
     float last_sample_ms_ = 0.0f;

@@ -49,6 +49,16 @@ struct LevelArgs {
     uint64_t* clock;          // mapped host memory: when the per-cube kernels began (device clock)
     uint32_t* host_seq;       // per segment, mapped host memory: set to seq once host_stats holds the decision
     uint32_t seq;             // number of this level, unlike any that came before
+    // the one-block level of a single integral lays out the next level itself
+    // (NULL: it does not): the children's ids, and the table in place of this
+    // level's own
+    uint64_t* ahead_uid;
+    uint32_t* ahead_uid_hi;
+    Segment* ahead_seg;
+    BSeg* ahead_bseg;
+    double2* ahead_prev;
+    int32_t* ahead_flags;
+    int64_t ahead_cap;        // children ahead_uid holds; with more the host lays the list out
 };
 
 // What next_list_kernel copies from mapped host memory into device memory for

@@ -208,8 +208,8 @@ __device__ __forceinline__ DecideIn decide_in(const LevelArgs& a, int si)
 }
 
 __device__ void seg_decide(const LevelArgs& a, int si);
-__device__ void decide_write(const LevelArgs& a, int si, const DecideIn& in, double accM, double accS2, double selM,
-                             double selS2, double margin, int64_t nsel, int bad);
+__device__ Decision decide_write(const LevelArgs& a, int si, const DecideIn& in, double accM, double accS2,
+                                 double selM, double selS2, double margin, int64_t nsel, int bad);
 
 // ---- finalize: per cube I_t = V * S1_t / N, m = mean I_t, s = std I_t ------
 // The partial sums of a pass's cubes are contiguous ([cube][trial *
@@ -533,8 +533,8 @@ __device__ void seg_decide(const LevelArgs& a, int si)
 
 // The segment's outcome from its totals (thread 0): stop rules, running
 // totals, the record in device memory and in the mapped host buffer.
-__device__ void decide_write(const LevelArgs& a, int si, const DecideIn& in, double accM, double accS2, double selM,
-                             double selS2, double margin, int64_t nsel, int bad)
+__device__ Decision decide_write(const LevelArgs& a, int si, const DecideIn& in, double accM, double accS2,
+                                 double selM, double selS2, double margin, int64_t nsel, int bad)
 {
     const Segment& sg = a.segs[si];
     {
@@ -550,7 +550,7 @@ __device__ void decide_write(const LevelArgs& a, int si, const DecideIn& in, dou
         S.n_sel = nsel;
         S.nonfinite = bad;
         S.range_lost = in.range_lost;
-        int32_t dec;
+        Decision dec;
         double totM = in.prev.x + accM, totS2 = in.prev.y + accS2;
         if (!sg.need_thr || nsel == 0) {
             dec = kDone;
@@ -576,10 +576,38 @@ __device__ void decide_write(const LevelArgs& a, int si, const DecideIn& in, dou
             __threadfence_system(); // the record is in host memory before its number is
             __hip_atomic_store(a.host_seq + si, a.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         }
+        return dec;
     }
 }
 
 __global__ __launch_bounds__(kLevelThreads) void seg_decide_kernel(const LevelArgs a) { seg_decide(a, blockIdx.x); }
+
+// The children of n_parents cubes (ids list, list_hi in LDS) in order, by the
+// whole block: child c of (hi:lo) is (hi:lo) * kids + c; with bisection
+// (hi:lo) << D | c.
+__device__ __forceinline__ void write_children(const uint64_t* list, const uint32_t* list_hi, int n_parents, int split,
+                                               int D, int64_t kids, uint64_t* out, uint32_t* out_hi)
+{
+    const int64_t n_writes = (int64_t)n_parents * kids;
+    if (split == 2) {
+        const uint64_t mask = (1ull << D) - 1ull;
+        for (int64_t w = threadIdx.x; w < n_writes; w += kLevelThreads) {
+            const uint64_t parent = list[w >> D];
+            out[w] = (parent << D) | ((uint64_t)w & mask);
+            if (out_hi) out_hi[w] = (list_hi[w >> D] << D) | (uint32_t)(parent >> (64 - D));
+        }
+    } else {
+        for (int64_t w = threadIdx.x; w < n_writes; w += kLevelThreads) {
+            const int64_t i = w / kids;
+            const uint64_t plo = list[i] * (uint64_t)kids;
+            const uint64_t lo = plo + (uint64_t)(w - i * kids);
+            out[w] = lo;
+            if (out_hi)
+                out_hi[w] = (uint32_t)((uint64_t)list_hi[i] * (uint64_t)kids + __umul64hi(list[i], (uint64_t)kids) +
+                                       (lo < plo ? 1u : 0u));
+        }
+    }
+}
 
 // ---- a whole small level in one launch ----------------------------------------
 // When every segment of the level is one tile (at most 1024 cubes) and no
@@ -590,12 +618,22 @@ __global__ __launch_bounds__(kLevelThreads) void seg_decide_kernel(const LevelAr
 // multi-launch path reduces a single tile record (the other threads add
 // zeros), so this is the same arithmetic in the same order and the results
 // are bitwise those of the multi-launch path.
+//
+// The level of a single integral also lays out the next one if it splits:
+// the children's ids and the table the host would send, so that the next
+// level starts with its sampling launch and not with a next-list kernel
+// before it (3.5 us and a gap, of 24 us for a level of a hundred cubes).
 __global__ __launch_bounds__(kLevelThreads) void level_small_kernel(const LevelArgs a)
 {
     __shared__ double sh[kWaves];
+    __shared__ uint64_t list[kTileCubes];
+    __shared__ uint32_t list_hi[kTileCubes];
+    __shared__ int shf[kWaves];
+    __shared__ int go_on;
     if (a.clock && blockIdx.x == 0 && threadIdx.x == 0) *a.clock = device_clock();
     const int si = blockIdx.x;
     const Segment& sg = a.segs[si];
+    const int slot = sg.slot, level = sg.level;
     const int64_t tile = sg.tile_base;
     const bool thr_on = sg.need_thr != 0;
     const DecideIn in = decide_in(a, si);
@@ -621,6 +659,7 @@ __global__ __launch_bounds__(kLevelThreads) void level_small_kernel(const LevelA
     }
     double accM = 0.0, accS2 = 0.0, selM = 0.0, selS2 = 0.0, margin = DBL_MAX;
     int64_t nsel = 0;
+    int sel_r[kPerThread] = {};
 #pragma unroll
     for (int j = 0; j < kPerThread; ++j) {
         const int64_t cl = threadIdx.x + (int64_t)j * kLevelThreads;
@@ -628,6 +667,7 @@ __global__ __launch_bounds__(kLevelThreads) void level_small_kernel(const LevelA
         const int64_t c = sg.cube_base + cl;
         const double m = m_r[j], s = s_r[j];
         const bool sel = thr_on && (s > thr);
+        sel_r[j] = sel;
         a.sel[c] = sel ? 1 : 0;
         if (sel) {
             selM += m;
@@ -657,7 +697,43 @@ __global__ __launch_bounds__(kLevelThreads) void level_small_kernel(const LevelA
             a.stats[si].sd = sdv;
             a.stats[si].thr = thr;
         }
-        decide_write(a, si, in, tot.accM, tot.accS2, tot.selM, tot.selS2, tot.margin, tot.nsel, bad);
+        const Decision dec =
+            decide_write(a, si, in, tot.accM, tot.accS2, tot.selM, tot.selS2, tot.margin, tot.nsel, bad);
+        // a non-finite integral ends here whatever its decision
+        go_on = dec == kSplit && !bad && tot.nsel * (int64_t)in.kids <= a.ahead_cap;
+    }
+    if (!a.ahead_uid) return;
+    __syncthreads();
+    if (!go_on) return;
+    const SlotDesc& sd = a.slots[slot];
+    int base = 0;
+#pragma unroll
+    for (int j = 0; j < kPerThread; ++j) {
+        int total;
+        const int pos = block_excl_scan_flag(sel_r[j], shf, &total);
+        if (sel_r[j]) {
+            const int64_t c = sg.cube_base + threadIdx.x + (int64_t)j * kLevelThreads;
+            list[base + pos] = a.uid[c];
+            list_hi[base + pos] = a.uid_hi ? a.uid_hi[c] : 0u;
+        }
+        base += total;
+    }
+    __syncthreads();
+    write_children(list, list_hi, base, sd.split, sd.dim, sd.kids, a.ahead_uid, a.ahead_uid_hi);
+    __syncthreads(); // every thread is past its reads of this level's segment
+    if (threadIdx.x == 0) {
+        const int64_t nn = (int64_t)base * sd.kids;
+        Segment g{};
+        g.slot = slot;
+        g.level = level + 1;
+        g.n_cubes = nn;
+        g.n_tiles = (nn + kTileCubes - 1) / kTileCubes;
+        g.need_thr = g.level < sd.max_depth ? 1 : 0;
+        if (g.need_thr && sd.scope == 1 && nn > sd.kids) g.group_size = sd.kids;
+        *a.ahead_seg = g;
+        *a.ahead_bseg = BSeg{0, 0, 0};
+        *a.ahead_prev = make_double2(in.prev.x + tot.accM, in.prev.y + tot.accS2);
+        *a.ahead_flags = 0;
     }
 }
 
@@ -694,29 +770,9 @@ __device__ void spawn_tile(const LevelArgs& a, int64_t tile)
         base += total;
     }
     __syncthreads();
-    const int64_t n_writes = (int64_t)base * kids;
     const int64_t first_out = sg.child_base + a.tiles[tile].sel_prefix * kids;
-    uint64_t* out = a.next_uid + first_out;
-    uint32_t* out_hi = a.next_uid_hi ? a.next_uid_hi + first_out : nullptr;
-    // child c of (hi:lo) is (hi:lo) * kids + c; with bisection (hi:lo) << D | c
-    if (sd.split == 2) {
-        const uint64_t mask = (1ull << D) - 1ull;
-        for (int64_t w = threadIdx.x; w < n_writes; w += kLevelThreads) {
-            const uint64_t parent = list[w >> D];
-            out[w] = (parent << D) | ((uint64_t)w & mask);
-            if (out_hi) out_hi[w] = (list_hi[w >> D] << D) | (uint32_t)(parent >> (64 - D));
-        }
-    } else {
-        for (int64_t w = threadIdx.x; w < n_writes; w += kLevelThreads) {
-            const int64_t i = w / kids;
-            const uint64_t plo = list[i] * (uint64_t)kids;
-            const uint64_t lo = plo + (uint64_t)(w - i * kids);
-            out[w] = lo;
-            if (out_hi)
-                out_hi[w] = (uint32_t)((uint64_t)list_hi[i] * (uint64_t)kids + __umul64hi(list[i], (uint64_t)kids) +
-                                       (lo < plo ? 1u : 0u));
-        }
-    }
+    write_children(list, list_hi, base, sd.split, D, kids, a.next_uid + first_out,
+                   a.next_uid_hi ? a.next_uid_hi + first_out : nullptr);
 }
 
 // ---- roots: uid = r for the d^D cubes of a newly admitted integral ----------
