@@ -465,8 +465,8 @@ struct Integrand<ZMC_MONOMIAL, D> {
 // which the host knows from a request's bounds and parameters; this form
 // checks each argument (the same value wherever it is in range).  The check
 // is a branch per point around the library's reduction for huge arguments,
-// which takes registers from the whole loop: the 6-D sine needs 149 VGPRs
-// with it and 115 without.
+// which takes registers from the whole loop: the 6-D sine needs 135 VGPRs
+// with it and 92 without.
 template <int F, int D>
 struct AnyArgument : Integrand<F, D> {};
 

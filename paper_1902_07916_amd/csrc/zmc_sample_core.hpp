@@ -10,13 +10,23 @@
 // 4-point groups g = chunk*G*64 + l + 64*j, j < G.  One group of 4 points uses
 // D Philox blocks (4*D words, point q dimension i = word q*D + i), so counter
 // word 0 of block k is g*D + k; the other three counter words and the key are
-// wave-uniform (SGPRs).  Each lane sums f and f^2 in FP64 and the wave
-// reduces with a fixed butterfly, so a unit's partial sums depend only on the
+// wave-uniform.  Each lane sums f (and f^2 on traced levels) in FP64 and the
+// wave reduces with a fixed butterfly, so a unit's partial sums depend only on the
 // unit and G.  The grid is persistent: wave w takes a contiguous range of
 // units; only the first unit's segment is found by binary search and only
 // its position decoded by division, later units follow by increments, and
 // a cube's corner and integrand constants are formed once for all of its
 // units.
+//
+// What bounds it: VALU issue.  Measured cycles per wave64 instruction and SIMD
+// with 8 waves: v_mad_u64_u32 and FP64 4.2; v_alignbit, v_bfi, v_min_f32,
+// v_rndne_f32 4.1; v_bitop3, v_xor, v_fma_f32 2.2-2.4 with vector operands
+// (two waves issue at once), 4.1-4.4 with a scalar one.  A v_mad issues beside
+// another wave's v_fma_f32 (2.9 each) but hardly beside a v_bitop3, nor does
+// FP64 (3.8 each).  A lone wave issues one instruction in 4.6 cycles, chained or not.
+// The 6-D sine in FP32 takes 338 instructions a group of 256 points: 5.75e11
+// points/s, 0.92 of the rate of its integer and FP64 instructions at one a
+// quad-cycle.
 //
 // An integrand class I provides P64 / P32 parameter blocks, prep64 / prep32
 // (per cube, from the slot descriptor and the cube corner), f64 / f32, the
