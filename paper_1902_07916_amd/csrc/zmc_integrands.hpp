@@ -115,6 +115,7 @@ struct Integrand;
 template <int D>
 struct Integrand<ZMC_GAUSS, D> {
     static constexpr bool kRangeCheck = true;
+    static constexpr bool kProduct = false;
     struct P64 {
         double mu[D], k, A;
     };
@@ -174,6 +175,7 @@ struct Integrand<ZMC_SIN_SUM, D> {
         int dummy;
     };
     static constexpr bool kRangeCheck = false; // |f| is not small over a cube: a sum near 0 is cancellation
+    static constexpr bool kProduct = false;
     struct P32 {
         float m[D], r0_hi, r0_lo;
         double scale;
@@ -204,6 +206,7 @@ struct Integrand<ZMC_SIN_SUM, D> {
 template <int D>
 struct Integrand<ZMC_GENZ_OSC, D> {
     static constexpr bool kRangeCheck = false; // as for the sine
+    static constexpr bool kProduct = false;
     struct P64 {
         double c[D], ph;
     };
@@ -243,6 +246,7 @@ struct Integrand<ZMC_GENZ_OSC, D> {
 template <int D>
 struct Integrand<ZMC_GENZ_PPEAK, D> {
     static constexpr bool kRangeCheck = true;
+    static constexpr bool kProduct = false;
     struct P64 {
         double e[D], w[D];
     };
@@ -297,6 +301,7 @@ struct Integrand<ZMC_GENZ_PPEAK, D> {
 template <int D>
 struct Integrand<ZMC_GENZ_CPEAK, D> {
     static constexpr bool kRangeCheck = true;
+    static constexpr bool kProduct = false;
     struct P64 {
         double c[D];
     };
@@ -343,6 +348,7 @@ struct Integrand<ZMC_GENZ_CPEAK, D> {
 template <int D>
 struct Integrand<ZMC_GENZ_GAUSS, D> {
     static constexpr bool kRangeCheck = true;
+    static constexpr bool kProduct = false;
     struct P64 {
         double c[D], w[D];
     };
@@ -399,6 +405,7 @@ struct Integrand<ZMC_GENZ_GAUSS, D> {
 template <int D>
 struct Integrand<ZMC_CONST, D> {
     static constexpr bool kRangeCheck = false;
+    static constexpr bool kProduct = false;
     struct P64 {
         double A;
     };
@@ -420,6 +427,7 @@ struct Integrand<ZMC_CONST, D> {
 template <int D>
 struct Integrand<ZMC_MONOMIAL, D> {
     static constexpr bool kRangeCheck = true;
+    static constexpr bool kProduct = true;
     struct P64 {
         int e[D];
     };

@@ -103,6 +103,7 @@ namespace zmc {
 template <int D>
 struct UserIntegrand {
     static constexpr bool kRangeCheck = true;
+    static constexpr bool kProduct = true; // it may be
     struct P64 {
         const double* prm;
     };

@@ -30,8 +30,9 @@
 //
 // An integrand class I provides P64 / P32 parameter blocks, prep64 / prep32
 // (per cube, from the slot descriptor and the cube corner), f64 / f32, the
-// FP64 scale P32::scale that multiplies each FP32 unit sum, and kRangeCheck
-// (whether its FP32 values can fall below FP32's normal range).
+// FP64 scale P32::scale that multiplies each FP32 unit sum, kRangeCheck
+// (whether its FP32 values can fall below FP32's normal range) and kProduct
+// (whether the last step of its FP32 value can be a product).
 #pragma once
 
 #include "zmc_device.hpp"
@@ -264,8 +265,9 @@ __device__ __forceinline__ void sample_units(const SampleArgs& a)
         // 1-2.4% faster than both the point-order sum and per-value FP64 adds
         // in a same-box A/B (and 0.5-3.7% slower at the other D).
         constexpr bool kPairSum = D == 6 || D == 7;
-        // nvalid: the lane's points of a ragged group that count
-        auto group = [&](auto ragged, int nvalid) {
+        // nvalid: the lane's points of a ragged group that count; rounded:
+        // the FP32 value is rounded before it is added (below)
+        auto group = [&](auto ragged, auto rounded, int nvalid) {
             constexpr bool kRagged = decltype(ragged)::value;
             [[maybe_unused]] float gs = 0.0f, gb = 0.0f;
             group_samples<D>(cb, c1, c2, c3, k0, k1, [&](int q, const uint32_t* w) {
@@ -274,6 +276,7 @@ __device__ __forceinline__ void sample_units(const SampleArgs& a)
 #pragma unroll
                     for (int i = 0; i < D; ++i) v[i] = unit_interval_f32(w[i]);
                     float f = I::f32(cs.p, v);
+                    if constexpr (decltype(rounded)::value) asm("" : "+v"(f));
                     if constexpr (kRagged) f = (q < nvalid) ? f : 0.0f;
                     if constexpr (kPairSum) {
                         if (q == 0) gs = f;
@@ -309,8 +312,22 @@ __device__ __forceinline__ void sample_units(const SampleArgs& a)
             if constexpr (FP32) S1 += (double)(kPairSum ? gs + gb : gs);
             cb += 64u * (uint32_t)D;
         };
-        for (int j = 0; j < n_whole; ++j) group(BoolTag<false>{}, 4);
-        if (pts & 255) group(BoolTag<true>{}, (pts & 255) - 4 * lane);
+        // An FP32 value that ends in a product can be fused into the group's
+        // sum, which then rounds once less (a sum of 256 points moves by some
+        // 1e-9).  Whether it is depends on the request alone: in full chunks
+        // up to D = 3, with a multiple of 4 points up to D = 9, never above.
+        constexpr bool kProduct = FP32 && I::kProduct;
+        bool fused = false;
+        if constexpr (kProduct && D <= 3) fused = pts == G * 256;
+        else if constexpr (kProduct && D <= 9) fused = (sd->samples & 3) == 0;
+        if (fused) {
+            // whole groups of 4 points only, the last for some lanes
+            const int n_lane = n_whole + ((pts & 255) > 4 * lane ? 1 : 0);
+            for (int j = 0; j < n_lane; ++j) group(BoolTag<false>{}, BoolTag<false>{}, 4);
+        } else {
+            for (int j = 0; j < n_whole; ++j) group(BoolTag<false>{}, BoolTag<kProduct>{}, 4);
+            if (pts & 255) group(BoolTag<true>{}, BoolTag<kProduct>{}, (pts & 255) - 4 * lane);
+        }
 
         S1 = wave_sum(S1);
         if constexpr (KEEP_S2) S2 = wave_sum(S2);

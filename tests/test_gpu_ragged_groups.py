@@ -33,3 +33,18 @@ def test_sums_match_oracle(z, orc, samples, dim, eval_):
     compare_tree(orc, w, r, 1e-9 if eval_ == "fp64" else 1e-4, 1e-6 if eval_ == "fp64" else 1e-4)
     plain = z.integrate(**w)
     assert (plain.integral, plain.std) == (r.integral, r.std)
+
+
+@pytest.mark.parametrize("dim,samples", [(2, 1027), (5, 1027), (5, 8193), (7, 1027), (7, 1022), (11, 1024), (11, 1027)])
+def test_product_rounded_before_the_sum(z, dim, samples):
+    """An FP32 value that ends in a product is rounded before it is added
+    where points are masked and from D = 10 on: the bits of a body that rounds
+    it itself."""
+    import paper_1902_07916_amd as pkg
+    head = "real t = 1; for (int i = 0; i < D; ++i) t += (real)p[0] * x[i]; "
+    w = dict(params=[0.7], lower=[0.0] * dim, upper=[1.0] * dim, divisions=2 if dim < 11 else 1, samples=samples,
+             trials=3, max_depth=0, sigma_mult=1.0, seed=7, eval="fp32")
+    print("product:", dim, samples, flush=True)
+    a = z.integrate(**w, integrand=pkg.register_integrand(head + "return t * x[0];", 1))
+    b = z.integrate(**w, integrand=pkg.register_integrand(head + 'real v = t * x[0]; asm("" : "+v"(v)); return v;', 1))
+    assert (a.integral, a.std, a.stderr) == (b.integral, b.std, b.stderr)
