@@ -180,7 +180,10 @@ int TileTable::load(const char* path)
         if (nf == 3 && g >= 1 && g <= 64) groups[f][d][e] = g;
         if (nf == 4 && w == 'w')
             for (int h = 0; h < kNumWaveHints; ++h)
-                if (kWaveHints[h] == (g == 7 || g == 8 ? 6 : g)) hint[f][d][e] = h;
+                if (kWaveHints[h] == (g == 7 || g == 8 ? 6 : g)) {
+                    hint[f][d][e] = h;
+                    given[f][d][e] = true;
+                }
         if (nf == 4 && w == 'b' && valid_block(g)) threads[f][d][e] = g;
     }
     return 0;
@@ -618,7 +621,7 @@ int Engine::step(hipStream_t st, const std::vector<LiveSeg>& live, uint64_t* cur
                 const int block = tiles_->block(L.integrand, L.dim, L.eval);
                 const int hint = sums        ? kSumsVariant
                                  : L.any_arg ? kAnyArgVariant
-                                             : tiles_->waves(L.integrand, L.dim, L.eval);
+                                             : tiles_->waves(L.integrand, L.dim, L.eval, L.units, L.unit_samples);
                 const int64_t cap = capacity(L.integrand, L.dim, L.eval, hint, block);
                 const int grid = (int)std::min<int64_t>(ceil_div(a.total_units, block / 64), cap);
                 ZMC_HIP(launch_sample(L.integrand, L.dim, L.eval, hint, grid, block, st, a));

@@ -76,6 +76,7 @@ private:
 struct TileTable {
     int groups[8][ZMC_MAX_DIM + 1][2];
     int hint[8][ZMC_MAX_DIM + 1][2];    // index into kWaveHints
+    bool given[8][ZMC_MAX_DIM + 1][2] = {}; // the hint is a tuning file's
     int threads[8][ZMC_MAX_DIM + 1][2]; // threads per sampling block
     TileTable();
     int load(const char* path); // 0 on success
@@ -84,9 +85,20 @@ struct TileTable {
         // run-time compiled user integrands use the default cap
         return (integrand >= 0 && integrand < 8) ? groups[integrand][dim][eval] : kDefaultGroups;
     }
-    int waves(int integrand, int dim, int eval) const
+    // The embedded table's variants were chosen on levels of 8e8 points and
+    // more, in units of 8192.  Most hold fewer registers by spilling in the
+    // code around a unit's points, which small units and small launches pay
+    // and the points don't repay: 10-D Genz Gaussian FP32, 177147 units,
+    // against the free kernel: 346 to 236 us at 250 points a unit, 630 to 613
+    // at 1000, 1124 to 1139 at 2000, 2132 to 2190 at 4096; 12-D, 12288 units:
+    // 66 to 27 us at 250, 208 to 188 at 4096, 375 to 363 at 8192 (1e8 points).
+    // So they run from 2048 points a unit and 2^28 a launch on; a tuning
+    // file's choice runs always.
+    int waves(int integrand, int dim, int eval, int64_t units, int64_t unit_samples) const
     {
-        return (integrand >= 0 && integrand < 8) ? hint[integrand][dim][eval] : 0;
+        if (integrand < 0 || integrand >= 8) return 0;
+        if (!given[integrand][dim][eval] && (unit_samples < 2048 || units < (1ll << 28) / unit_samples)) return 0;
+        return hint[integrand][dim][eval];
     }
     int block(int integrand, int dim, int eval) const
     {

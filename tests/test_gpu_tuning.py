@@ -61,3 +61,15 @@ def test_unit_size_changes_only_rounding(tmp_path):
         assert tuple(r.cubes_per_level) == tuple(base.cubes_per_level)
         assert abs(r.integral - base.integral) <= 1e-12 * max(abs(base.integral), base.std)
         assert abs(r.std - base.std) <= 1e-12 * base.std
+
+
+@pytest.mark.parametrize("samples,waves", [(250, 5), (2048, 5), (32768, 1)])
+def test_variant_by_launch_size_bitwise(tmp_path, samples, waves):
+    """The embedded table's variant runs in large launches only (here from
+    2^28 points on, the last case); a file's always: the same results."""
+    w = dict(integrand=5, params=[0.3] * 24, lower=[0.0] * 12, upper=[1.0] * 12, divisions=2, samples=samples,
+             trials=3, max_depth=0, sigma_mult=3.0, seed=5, eval="fp32")
+    print("variant by launch size:", samples, flush=True)
+    a, b = _run(tmp_path, {}, w), _run(tmp_path, {"5:12:1:w": waves}, w)
+    assert a.status == b.status == 0
+    assert (a.integral, a.std, a.stderr) == (b.integral, b.std, b.stderr)
