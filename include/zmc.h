@@ -47,7 +47,9 @@
  *    pinned host staging buffers);
  *  - `stream` is a hipStream_t owned by the caller (NULL = the default
  *    stream); the library enqueues on it and, for synchronous calls, waits
- *    for its work there before returning.
+ *    there until all that the call reads and writes is read and written
+ *    (the last kernel may still be leaving the stream); calls may change
+ *    stream from one to the next.
  */
 #ifndef ZMC_H
 #define ZMC_H
@@ -272,9 +274,10 @@ int zmc_integrate_request(const zmc_request* req, void* stream, zmc_result* out,
  * those of zmc_integrate_request() (the same kernels).  Calls share that one
  * array and keep no state in it between calls (the level counters it holds
  * are left at zero by every launch); the library serialises them, and each
- * call waits for its last kernel's records before returning, so calls do not
- * overlap on the device: a caller that replays such a call asynchronously (e.g. from a
- * captured graph) must not let two of them run at once.
+ * call waits for its last kernel's record, which is written behind all its
+ * other stores, before returning, so no two calls use the array at once: a
+ * caller that replays such a call asynchronously (e.g. from a captured graph)
+ * must not let two of them run at once.
  * ENOMEM (before any device work, with the sizes in zmc_strerror) when the
  * request's worst-case tree (zmc_request_bytes) exceeds the static array;
  * EINVAL for a run-time compiled integrand (loading its code allocates) and

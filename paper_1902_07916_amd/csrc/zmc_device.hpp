@@ -348,6 +348,12 @@ struct OpMax {
     __device__ __forceinline__ double operator()(double a, double b) const { return fmax(a, b); }
 };
 
+// Wait until the L2 cache holds every store this wave has issued.  A barrier
+// alone lets other waves' stores be under way; a thread that releases its
+// block's results to the host or to another block with a fence of its own
+// therefore does so behind this and a barrier.
+__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 __device__ __forceinline__ double wave_sum(double v) { return wave_reduce(v, OpAdd{}); }
 
 // ---------------------------------------------------------------------------

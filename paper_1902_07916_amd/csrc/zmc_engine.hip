@@ -335,8 +335,10 @@ int Engine::upload_slot(int slot, hipStream_t st)
 
 // Wait for the records of the level just launched (ns segments).  The kernels
 // write each segment's record and then the level's number into mapped host
-// memory; they are the level's last, so once every number is there nothing
-// of the level is outstanding.
+// memory, behind every other store of the level, so once all numbers are there
+// the level's memory may be used by anything, on any stream.  Only a next level
+// laid out ahead (tail_) is written after the number: what uses it follows on
+// the same stream, and drive() does not return before it is there.
 int Engine::wait_level(hipStream_t st, int ns)
 {
     const double t0 = now_ms();
@@ -729,6 +731,7 @@ int Engine::step(hipStream_t st, const std::vector<LiveSeg>& live, uint64_t* cur
         const int rc = wait_level(st, ns);
         if (rc != ZMC_OK) return rc;
         last_sample_ms_ = (float)((double)(h_clock_[1] - h_clock_[0]) * clock_ms_);
+        tail_ = ahead_uid_ && h_stats_[0].decision == kSplit;
     }
     return ZMC_OK;
 }
@@ -841,6 +844,17 @@ int Engine::next_list(hipStream_t st, std::vector<LiveSeg>& live, const std::vec
 // Shared level loop of run() and serving.
 int Engine::drive(hipStream_t st, int n_slots, Admission& adm, zmc_trace* trace, const std::atomic<bool>* stop_flag,
                   std::atomic<uint64_t>* levels_stepped)
+{
+    tail_ = false;
+    const int rc = drive_levels(st, n_slots, adm, trace, stop_flag, levels_stepped);
+    // an integral that ends at its own decision leaves nothing on the stream;
+    // one that is stopped or cancelled, or a failed launch, may
+    if (rc != ZMC_OK || tail_) (void)hipStreamSynchronize(st);
+    return rc;
+}
+
+int Engine::drive_levels(hipStream_t st, int n_slots, Admission& adm, zmc_trace* trace,
+                         const std::atomic<bool>* stop_flag, std::atomic<uint64_t>* levels_stepped)
 {
     std::vector<int> free_ids;
     for (int i = n_slots - 1; i >= 0; --i) free_ids.push_back(i);

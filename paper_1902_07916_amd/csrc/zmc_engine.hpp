@@ -182,6 +182,8 @@ public:
     int groups_of(const zmc_request& r) const;
 
 private:
+    int drive_levels(hipStream_t st, int n_slots, Admission& adm, zmc_trace* trace, const std::atomic<bool>* stop_flag,
+                     std::atomic<uint64_t>* levels_stepped);
     void fill_slot_desc(int slot, const zmc_request& r);
     int upload_slot(int slot, hipStream_t st);
     int wait_level(hipStream_t st, int ns);
@@ -254,6 +256,7 @@ private:
     uint32_t* ahead_hi_ = nullptr;
     int64_t ahead_cap_ = 0;         // children it holds
     bool table_ready_ = false;      // the device holds the next level's list and table
+    bool tail_ = false;             // the last level's kernel may still be writing them
     std::vector<int> pend_slots_; // newly admitted integrals whose descriptors go up with it
     // GPU time of the last level's sampling launches
     float last_sample_ms_ = 0.0f;

@@ -131,6 +131,7 @@ __device__ __forceinline__ int seg_of_tile(const Segment* segs, int n, int64_t t
 __device__ bool last_tile_of_segment(int32_t* count, int si, int64_t n_tiles)
 {
     __shared__ int last;
+    stores_done();
     __syncthreads();
     // a one-tile segment has no other block to wait for: its own record is
     // visible to the block after the barrier, and no device-scope fence (an
@@ -528,11 +529,18 @@ __device__ void seg_decide(const LevelArgs& a, int si)
         carry += chunk;
     }
 
+    // the record is the last a segment's block writes: behind every wave's prefixes
+    stores_done();
+    __syncthreads();
     if (threadIdx.x == 0) decide_write(a, si, in, accM, accS2, selM, selS2, margin, nsel, bad);
 }
 
 // The segment's outcome from its totals (thread 0): stop rules, running
-// totals, the record in device memory and in the mapped host buffer.
+// totals, the record in device memory and in the mapped host buffer, then the
+// level's number there.  The host goes on once it sees the number, and a call
+// may end there, so what the segment's blocks store they store before it (the
+// caller waits for its waves' stores; the fence here writes them back).  The
+// one exception is the next level laid out ahead, see level_small_kernel.
 __device__ Decision decide_write(const LevelArgs& a, int si, const DecideIn& in, double accM, double accS2,
                                  double selM, double selS2, double margin, int64_t nsel, int bad)
 {
@@ -679,6 +687,7 @@ __global__ __launch_bounds__(kLevelThreads) void level_small_kernel(const LevelA
         }
         if (thr_on && thr > 0.0) margin = fmin(margin, fabs(s - thr) / thr);
     }
+    stores_done(); // ahead of the reduction's barriers: the record goes out behind every wave's stores
     const SelTotals tot = block_reduce_sel(SelTotals{accM, accS2, selM, selS2, margin, nsel});
     if (threadIdx.x == 0) {
         TileRec& T = a.tiles[tile];
