@@ -375,17 +375,22 @@ int Engine::wait_level(hipStream_t st, int ns)
 // rounded up to 256 bytes.
 size_t Engine::reservation_bytes(const zmc_request& r) const { return request_bytes(r, *tiles_); }
 
-size_t request_bytes(const zmc_request& r, const TileTable& t)
+int64_t next_level_most(const zmc_request& r, int64_t n)
 {
     const int64_t cap = r.max_cubes_per_level > 0 ? r.max_cubes_per_level : ZMC_DEFAULT_MAX_CUBES;
+    const double frac = r.sigma_mult > 0 ? 1.0 / (1.0 + r.sigma_mult * r.sigma_mult) : 1.0;
+    int64_t nsel = (int64_t)floor((double)n * frac);
+    if (r.sigma_mult == 0.0) nsel = n - 1;
+    const int64_t nn = nsel * kids_of(r);
+    return nn > cap || nn < 0 ? cap : nn;
+}
+
+size_t request_bytes(const zmc_request& r, const TileTable& t)
+{
     const int64_t k = (int64_t)ipow_u64((uint64_t)r.divisions_per_axis, r.dim);
     int64_t n = k, worst = k, worst_next = 0;
     for (int l = 0; l < r.max_depth; ++l) {
-        const double frac = r.sigma_mult > 0 ? 1.0 / (1.0 + r.sigma_mult * r.sigma_mult) : 1.0;
-        int64_t nsel = (int64_t)floor((double)n * frac);
-        if (r.sigma_mult == 0.0) nsel = n - 1;
-        int64_t nn = nsel * kids_of(r);
-        if (nn > cap || nn < 0) nn = cap;
+        const int64_t nn = next_level_most(r, n);
         worst_next = std::max(worst_next, nn);
         worst = std::max(worst, nn);
         n = nn;
@@ -657,23 +662,20 @@ int Engine::step(hipStream_t st, const std::vector<LiveSeg>& live, uint64_t* cur
     la.clock = d_hclock_ + 1;
     la.host_seq = d_hseq_;
     la.seq = ++seq_;
-    ahead_uid_ = nullptr;
-    ahead_hi_ = nullptr;
+    ahead_ = nullptr;
     if (!stats_only && !trace && ns == 1 && tile == 1 && h_segs_[0].need_thr && groups == 0) {
-        // room for the children of every cube that Cantelli's inequality lets
-        // exceed the threshold (in exact arithmetic: the kernel and
+        // room for the largest next level that the request's reservation
+        // counts with (rounding can take the kernel past it: the kernel and
         // next_list() check the count against the room)
         const HostSlot& hs = slots_[live[0].slot];
-        const double sm = hs.req.sigma_mult;
-        const int64_t most = sm > 0.0 ? (int64_t)((double)cube / (1.0 + sm * sm)) + 1 : cube;
-        const int64_t n = most * kids_of(hs.req);
-        if (n <= kAheadMax) {
-            uint64_t* u = (uint64_t*)arena_.alloc(cur_side ^ 1, (size_t)n * sizeof(uint64_t));
-            uint32_t* h = u && hs.wide ? (uint32_t*)arena_.alloc(cur_side ^ 1, (size_t)n * sizeof(uint32_t)) : nullptr;
-            if (u && (h || !hs.wide)) {
-                la.ahead_uid = ahead_uid_ = u;
+        const int64_t n = next_level_most(hs.req, cube);
+        if (n > 0 && n <= kAheadMax) {
+            ahead_ = (char*)arena_.alloc(cur_side ^ 1, (size_t)AheadList::bytes(n, hs.wide));
+            if (ahead_) {
+                la.ahead = ahead_;
+                la.ahead_side = cur_side ^ 1;
+                la.ahead_wide = hs.wide ? 1 : 0;
                 la.ahead_cap = ahead_cap_ = n;
-                la.ahead_uid_hi = ahead_hi_ = h;
                 la.ahead_seg = d_segs_;
                 la.ahead_bseg = d_bsegs_;
                 la.ahead_prev = d_prev_;
@@ -731,7 +733,7 @@ int Engine::step(hipStream_t st, const std::vector<LiveSeg>& live, uint64_t* cur
         const int rc = wait_level(st, ns);
         if (rc != ZMC_OK) return rc;
         last_sample_ms_ = (float)((double)(h_clock_[1] - h_clock_[0]) * clock_ms_);
-        tail_ = ahead_uid_ && h_stats_[0].decision == kSplit;
+        tail_ = ahead_ && h_stats_[0].decision == kSplit;
     }
     return ZMC_OK;
 }
@@ -746,23 +748,31 @@ int Engine::next_list(hipStream_t st, std::vector<LiveSeg>& live, const std::vec
     int64_t total = 0;
     const int ns = (int)live.size();
     const int other = cur_side ^ 1;
-    if (ahead_uid_ && ns == 1 && split[0] && fresh.empty() &&
+    if (ahead_ && ns == 1 && split[0] && fresh.empty() &&
         h_stats_[0].n_sel * kids_of(slots_[live[0].slot].req) <= ahead_cap_) {
-        // the level kernel wrote this list and its table
+        // the level kernel wrote this list and its table; the list's own
+        // bytes stay allocated, the rest of the block is given back
         HostSlot& hs = slots_[live[0].slot];
-        live[0].n_cubes = h_stats_[0].n_sel * kids_of(hs.req);
+        const int64_t n = h_stats_[0].n_sel * kids_of(hs.req);
+        const AheadList at = AheadList::place(n, ahead_cap_, hs.wide, other);
+        arena_.reset(other);
+        cur_uid = (uint64_t*)arena_.alloc(other, (size_t)n * sizeof(uint64_t));
+        cur_hi_ = hs.wide ? (uint32_t*)arena_.alloc(other, (size_t)n * sizeof(uint32_t)) : nullptr;
+        if ((char*)cur_uid != ahead_ + at.uid || (hs.wide && (char*)cur_hi_ != ahead_ + at.hi)) {
+            set_error("internal: a list laid out ahead is not where it was allocated");
+            return ZMC_EINVAL;
+        }
+        live[0].n_cubes = n;
         hs.level += 1;
         arena_.reset(cur_side);
         cur_side = other;
-        cur_uid = ahead_uid_;
-        cur_hi_ = ahead_hi_;
-        ahead_uid_ = nullptr;
+        ahead_ = nullptr;
         table_ready_ = true;
         return ZMC_OK;
     }
-    if (ahead_uid_) {
+    if (ahead_) {
         arena_.reset(other); // not needed: new integrals join, or the integral ended
-        ahead_uid_ = nullptr;
+        ahead_ = nullptr;
     }
     bool any_split = false;
     for (int i = 0; i < ns; ++i) any_split |= split[i] != 0;
@@ -863,7 +873,7 @@ int Engine::drive_levels(hipStream_t st, int n_slots, Admission& adm, zmc_trace*
     cur_hi_ = nullptr;
     pend_next_ = false;
     pend_slots_.clear();
-    ahead_uid_ = nullptr;
+    ahead_ = nullptr;
     table_ready_ = false;
     int cur_side = 0;
     arena_.reset(0);
@@ -1054,7 +1064,7 @@ int Engine::cube_estimates(const zmc_request& req, int level, const uint64_t* ui
     if (!d_uid) return ZMC_ENOMEM;
     cur_hi_ = nullptr; // ids given here are below 2^64
     pend_next_ = false;
-    ahead_uid_ = nullptr;
+    ahead_ = nullptr;
     table_ready_ = false;
     ZMC_HIP(hipMemcpyAsync(d_uid, uids, (size_t)n * 8, hipMemcpyHostToDevice, st));
     std::vector<LiveSeg> live{{0, n}};

@@ -133,7 +133,9 @@ constexpr int64_t ZMC_DEFAULT_MAX_CUBES = 1LL << 24;
 // (cube, trial), of a request under a tile table.
 int groups_for(const zmc_request& r, const TileTable& t);
 int chunks_for(const zmc_request& r, const TileTable& t);
-// Worst-case device bytes of one request's tree (see Engine::reservation_bytes).
+// The most cubes a level of n can be followed by, and the worst-case device
+// bytes of one request's tree (see Engine::reservation_bytes).
+int64_t next_level_most(const zmc_request& r, int64_t n);
 size_t request_bytes(const zmc_request& r, const TileTable& t);
 bool wide_ids(const zmc_request& r);
 bool any_argument(const zmc_request& r);
@@ -251,9 +253,8 @@ private:
     RootArgs pend_ra_{};
     int pend_n_up_ = 0;
     int pend_n_spawn_segs_ = 0;
-    // the next list laid out ahead by the level kernel (LevelArgs::ahead_uid)
-    uint64_t* ahead_uid_ = nullptr; // of the level last stepped, NULL if it was not
-    uint32_t* ahead_hi_ = nullptr;
+    // the next list laid out ahead by the level kernel (LevelArgs::ahead)
+    char* ahead_ = nullptr;         // its block, of the level last stepped; NULL if it was not
     int64_t ahead_cap_ = 0;         // children it holds
     bool table_ready_ = false;      // the device holds the next level's list and table
     bool tail_ = false;             // the last level's kernel may still be writing them

@@ -50,15 +50,36 @@ struct LevelArgs {
     uint32_t* host_seq;       // per segment, mapped host memory: set to seq once host_stats holds the decision
     uint32_t seq;             // number of this level, unlike any that came before
     // the one-block level of a single integral lays out the next level itself
-    // (NULL: it does not): the children's ids, and the table in place of this
-    // level's own
-    uint64_t* ahead_uid;
-    uint32_t* ahead_uid_hi;
+    // (ahead NULL: it does not): the children's ids into this block, where
+    // the host would have allocated lists of their number (AheadList), and the
+    // table in place of this level's own
+    char* ahead;
+    int32_t ahead_side;       // end of the arena that the block was taken from
+    int32_t ahead_wide;       // the ids take a second array
     Segment* ahead_seg;
     BSeg* ahead_bseg;
     double2* ahead_prev;
     int32_t* ahead_flags;
-    int64_t ahead_cap;        // children ahead_uid holds; with more the host lays the list out
+    int64_t ahead_cap;        // children the block holds; with more the host lays the list out
+};
+
+// The lists of n children within a block for `cap` of them: at its lower end
+// for side 0 of the arena, at its upper end for side 1, the upper id words
+// after (before, for side 1) the lower ones, each in whole 256 bytes.  So the
+// host can give the block back and take the n children's bytes alone, and the
+// next level leaves as much of the arena as with a list that the host laid out.
+struct AheadList {
+    int64_t uid, hi; // byte offsets
+    __host__ __device__ static constexpr int64_t padded(int64_t bytes) { return (bytes + 255) & ~(int64_t)255; }
+    __host__ __device__ static constexpr int64_t bytes(int64_t n, bool wide)
+    {
+        return padded(n * (int64_t)sizeof(uint64_t)) + (wide ? padded(n * (int64_t)sizeof(uint32_t)) : 0);
+    }
+    __host__ __device__ static constexpr AheadList place(int64_t n, int64_t cap, bool wide, int side)
+    {
+        const int64_t u = padded(n * (int64_t)sizeof(uint64_t));
+        return side == 0 ? AheadList{0, u} : AheadList{bytes(cap, wide) - u, bytes(cap, wide) - bytes(n, wide)};
+    }
 };
 
 // What next_list_kernel copies from mapped host memory into device memory for

@@ -711,7 +711,7 @@ __global__ __launch_bounds__(kLevelThreads) void level_small_kernel(const LevelA
         // a non-finite integral ends here whatever its decision
         go_on = dec == kSplit && !bad && tot.nsel * (int64_t)in.kids <= a.ahead_cap;
     }
-    if (!a.ahead_uid) return;
+    if (!a.ahead) return;
     __syncthreads();
     if (!go_on) return;
     const SlotDesc& sd = a.slots[slot];
@@ -728,10 +728,12 @@ __global__ __launch_bounds__(kLevelThreads) void level_small_kernel(const LevelA
         base += total;
     }
     __syncthreads();
-    write_children(list, list_hi, base, sd.split, sd.dim, sd.kids, a.ahead_uid, a.ahead_uid_hi);
+    const int64_t nn = (int64_t)base * sd.kids;
+    const AheadList at = AheadList::place(nn, a.ahead_cap, a.ahead_wide != 0, a.ahead_side);
+    write_children(list, list_hi, base, sd.split, sd.dim, sd.kids, (uint64_t*)(a.ahead + at.uid),
+                   a.ahead_wide ? (uint32_t*)(a.ahead + at.hi) : nullptr);
     __syncthreads(); // every thread is past its reads of this level's segment
     if (threadIdx.x == 0) {
-        const int64_t nn = (int64_t)base * sd.kids;
         Segment g{};
         g.slot = slot;
         g.level = level + 1;
