@@ -104,6 +104,19 @@ struct RootArgs {
     uint32_t* uid_hi; // written 0 when not NULL
 };
 
+// Threads per block of the per-cube kernels, two cubes of a tile each.  A small
+// level has few tiles and waits for each block's chain of loads, divisions and
+// reductions: finalize over 8 tiles takes 18.0 us with 256 threads, 13.5 with
+// 512 and 13.5 with 1024, the selection 8.7, 9.8 and 13.2 (its barriers wait
+// for more waves); over 464 tiles finalize takes 35, 27 and 48.
+constexpr int kLevelThreads = 512;
+
+// The doubles (40 KiB) that finalize stages in LDS: a row for each thread's
+// cube where a row of n values fits.  Compared by division: trials times
+// chunks reaches 2^29 and more.
+constexpr int kStage = 5120;
+__host__ __device__ constexpr bool row_fits(int64_t n) { return n <= kStage / kLevelThreads; }
+
 // Launchers; each returns the hipError_t of its launch.
 // Occupancy variants of every sampling kernel: the waves per SIMD the
 // register allocator and the scheduler aim at (1 = no constraint).  Most

@@ -27,12 +27,6 @@ namespace zmc {
 
 namespace {
 
-// Threads per block of the per-cube kernels, two cubes of a tile each.  A small
-// level has few tiles and waits for each block's chain of loads, divisions and
-// reductions: finalize over 8 tiles takes 18.0 us with 256 threads, 13.5 with
-// 512 and 13.5 with 1024, the selection 8.7, 9.8 and 13.2 (its barriers wait
-// for more waves); over 464 tiles finalize takes 35, 27 and 48.
-constexpr int kLevelThreads = 512;
 constexpr int kWaves = kLevelThreads / 64;
 constexpr int kPerThread = kTileCubes / kLevelThreads;
 
@@ -221,7 +215,6 @@ __device__ Decision decide_write(const LevelArgs& a, int si, const DecideIn& in,
 // deviations.  Wider rows (many trials or chunks) are read from memory, only
 // their trial values kept in LDS, or formed again for each of the three sums
 // where those do not fit either.
-constexpr int kStage = 5120; // 40 KiB of doubles: rows of up to 10 values
 
 // KEEP: also leave each thread's cubes' m and s in m_r / s_r (pass j at
 // index j), for the one-block level path.
@@ -237,9 +230,9 @@ __device__ void finalize_tile(const LevelArgs& a, int64_t tile, int si, double* 
     const Segment& sg = a.segs[si];
     const SlotDesc& sd = a.slots[sg.slot];
     const int D = sd.dim, n1 = sd.trials, nch = sd.nch;
-    const int per = n1 * nch; // partials per cube
-    const bool staged = per * kLevelThreads <= kStage;
-    const bool rows = n1 * kLevelThreads <= kStage; // the trial values fit LDS
+    const int64_t per = (int64_t)n1 * nch; // partials per cube
+    const bool staged = row_fits(per);
+    const bool rows = row_fits(n1); // the trial values fit LDS
     const double V = cube_volume(sd, D, sg.level);
     const double N = (double)sd.samples;
     const int64_t first = (tile - sg.tile_base) * kTileCubes;
@@ -253,23 +246,23 @@ __device__ void finalize_tile(const LevelArgs& a, int64_t tile, int si, double* 
         const double2* src = a.partial + sg.part_base + c0 * per;
         if (staged) {
             __syncthreads(); // the previous pass is done with the stage
-            for (int e = threadIdx.x; e < cnt * per; e += kLevelThreads) stage[e] = src[e].x;
+            for (int e = threadIdx.x; e < cnt * (int)per; e += kLevelThreads) stage[e] = src[e].x;
             __syncthreads();
         }
         if ((int)threadIdx.x >= cnt) continue;
         const int64_t cl = c0 + threadIdx.x;
         const int64_t c = sg.cube_base + cl;
         const double2* P = src + (int64_t)threadIdx.x * per;
-        double* row = stage + threadIdx.x * (staged ? per : n1); // this thread's alone from here on
+        double* row = stage + threadIdx.x * (staged ? (int)per : n1); // this thread's alone from here on
         auto S1_mem = [&](int t) {
             double S1 = 0.0;
-            for (int ch = 0; ch < nch; ++ch) S1 += P[t * nch + ch].x;
+            for (int ch = 0; ch < nch; ++ch) S1 += P[(int64_t)t * nch + ch].x;
             return S1;
         };
         if (a.tr_S1) {
             for (int t = 0; t < n1; ++t) {
                 double S2 = 0.0;
-                for (int ch = 0; ch < nch; ++ch) S2 += P[t * nch + ch].y;
+                for (int ch = 0; ch < nch; ++ch) S2 += P[(int64_t)t * nch + ch].y;
                 a.tr_S1[c * n1 + t] = S1_mem(t);
                 a.tr_S2[c * n1 + t] = S2;
             }
