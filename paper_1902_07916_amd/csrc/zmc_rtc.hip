@@ -11,8 +11,8 @@
 // (the request's params) and D.  The body is compiled once per (D, eval) on
 // first use, around the same sampling body as the precompiled registry
 // (zmc_sample_core.hpp), and once more with the sums of squares kept if a level
-// is traced (a conversion and an FP64 FMA per point: bodies of 3 to 9
-// dimensions ran 2-8% faster without, a 6- and a 9-D FP32 Gaussian 2% slower);
+// is traced (a conversion and an FP64 FMA per point: FP32 Gaussian bodies of 1
+// to 16 dimensions run 1-7% faster without, FP64 ones 0-2%);
 // the device headers are embedded in the library at
 // build time, so nothing is read from disk at run time.
 #include <hip/hip_runtime.h>
@@ -43,6 +43,25 @@ struct Compiled {
     int capacity = 0;
 };
 
+// FP32 kernels run four waves per SIMD at least: always from kFourWavesMinD
+// dimensions on, below where the compiler's free choice takes more than
+// kFourWavesRegs registers, which leaves three.  Against the free choice, in
+// 1e9 points/s: Gaussian bodies at D = 9, 10 and 12 283 -> 292, 274 -> 284,
+// 236 -> 242; a body of three D x D products, which spills by the bound (128
+// registers and up to 720 bytes a lane, for up to 256 registers), at D = 9,
+// 12, 14 and 16 19.8 -> 20.5, 12.2 -> 12.9, 4.1 -> 4.8, 7.0 -> 6.9, and at
+// D = 3 and 7 157 -> 181 and 33.6 -> 35.5.  A body that fits anyway can lose:
+// 1.4% with a Gaussian of 67 registers at D = 3.
+constexpr int kFourWavesMinD = 8;
+constexpr int kFourWavesRegs = 128;
+// From kHalvesMinD dimensions on the words of a whole group take too many
+// registers under the compiler's own schedule: in halves the FP32 Gaussian
+// body at D = 14 takes 126 of them for 146 (198 -> 207e9 points/s), at D = 16
+// spills 20 bytes for 84 (154 -> 158), and the same at D = 12 in FP64 140 for
+// 150 (180, 180); a body of D (D - 1) / 2 quotients at D = 16 22.3 -> 22.6.
+// At D = 8 and 9 halves gain 0-4% with bodies that spill and lose 0-3% with others.
+constexpr int kHalvesMinD = 10;
+
 std::mutex g_mu;
 std::vector<UserDef> g_defs;
 std::map<std::tuple<int, int, int, bool>, Compiled> g_cache; // (id, D, eval, sums of squares kept)
@@ -55,15 +74,13 @@ typedef __hip_internal::int32_t int32_t;
 typedef __hip_internal::uint8_t uint8_t;
 )ZMCRTC";
 
-std::string program_source(const std::string& body, int dim, bool fp32, bool keep_s2)
+std::string program_source(const std::string& body, int dim, bool fp32, bool keep_s2, bool four_waves)
 {
     std::string s = kPrelude;
     s += "#define ZMC_D " + std::to_string(dim) + "\n";
     s += "#define ZMC_FP32 " + std::string(fp32 ? "true" : "false") + "\n";
-    // four waves per SIMD where many FP32 words are live (9-D Gaussian body
-    // 2.85e11 -> 2.89e11 points/s); fewer registers than that leave none for
-    // a larger body, and at D = 3 the bound costs 4%
-    s += "#define ZMC_OCCUPANCY " + std::string(fp32 && dim >= 8 ? "__attribute__((amdgpu_waves_per_eu(4)))" : "") + "\n";
+    s += "#define ZMC_OCCUPANCY " + std::string(four_waves ? "__attribute__((amdgpu_waves_per_eu(4)))" : "") + "\n";
+    s += "#define ZMC_HALVES " + std::string(dim >= kHalvesMinD ? "true" : "false") + "\n";
     s += "#define ZMC_KEEP_S2 " + std::string(keep_s2 ? "true" : "false") + "\n";
     s += R"ZMCRTC(
 #include "zmc_sample_core.hpp"
@@ -134,7 +151,7 @@ struct UserIntegrand {
 } // namespace zmc
 extern "C" __global__ __launch_bounds__(256) ZMC_OCCUPANCY void zmc_user_kernel(const zmc::SampleArgs a)
 {
-    zmc::sample_units<zmc::UserIntegrand<ZMC_D>, ZMC_D, ZMC_FP32, ZMC_KEEP_S2>(a);
+    zmc::sample_units<zmc::UserIntegrand<ZMC_D>, ZMC_D, ZMC_FP32, ZMC_KEEP_S2, ZMC_HALVES>(a);
 }
 )ZMCRTC";
     return s;
@@ -142,9 +159,10 @@ extern "C" __global__ __launch_bounds__(256) ZMC_OCCUPANCY void zmc_user_kernel(
 
 // Compile one variant to a code object; returns 0 and fills `code`, or -1
 // with the compiler log in `log`.
-int compile(const std::string& body, int dim, bool fp32, bool keep_s2, std::vector<char>& code, std::string& log)
+int compile(const std::string& body, int dim, bool fp32, bool keep_s2, bool four_waves, std::vector<char>& code,
+            std::string& log)
 {
-    const std::string src = program_source(body, dim, fp32, keep_s2);
+    const std::string src = program_source(body, dim, fp32, keep_s2, four_waves);
     hiprtcProgram prog;
     if (hiprtcCreateProgram(&prog, src.c_str(), "zmc_user.hip", kRtcHeaderCount, kRtcHeaderSources,
                             kRtcHeaderNames) != HIPRTC_SUCCESS) {
@@ -188,7 +206,7 @@ int rtc_register(const char* body, int n_params, int* id)
     // compile once (D = 4, FP64) so that syntax errors surface now
     std::vector<char> code;
     std::string log;
-    if (compile(body, 4, false, false, code, log) != 0) {
+    if (compile(body, 4, false, false, false, code, log) != 0) {
         set_error("user integrand does not compile:\n" + log);
         return ZMC_EINVAL;
     }
@@ -231,24 +249,35 @@ static int rtc_get(int id, int dim, int eval, bool keep_s2, Compiled& out)
         }
         body = g_defs[k].body;
     }
-    std::vector<char> code;
-    std::string log;
-    if (compile(body, dim, eval == ZMC_EVAL_FP32, keep_s2, code, log) != 0) {
-        set_error("user integrand does not compile:\n" + log);
-        return ZMC_EINVAL;
+    const bool fp32 = eval == ZMC_EVAL_FP32;
+    bool four_waves = fp32 && dim >= kFourWavesMinD;
+    Compiled c;
+    while (true) {
+        std::vector<char> code;
+        std::string log;
+        if (compile(body, dim, fp32, keep_s2, four_waves, code, log) != 0) {
+            set_error("user integrand does not compile:\n" + log);
+            return ZMC_EINVAL;
+        }
+        hipError_t e = hipModuleLoadData(&c.module, code.data());
+        if (e == hipSuccess) e = hipModuleGetFunction(&c.fn, c.module, "zmc_user_kernel");
+        if (e != hipSuccess) {
+            set_error(std::string("loading the user kernel: ") + hipGetErrorString(e));
+            return ZMC_EDEVICE;
+        }
+        int regs = 0;
+        if (!fp32 || four_waves || hipFuncGetAttribute(&regs, HIP_FUNC_ATTRIBUTE_NUM_REGS, c.fn) != hipSuccess ||
+            regs <= kFourWavesRegs)
+            break;
+        (void)hipModuleUnload(c.module);
+        four_waves = true;
     }
     std::lock_guard<std::mutex> lk(g_mu);
     auto it = g_cache.find(key);
     if (it != g_cache.end()) { // built meanwhile by another thread
+        (void)hipModuleUnload(c.module);
         out = it->second;
         return ZMC_OK;
-    }
-    Compiled c;
-    hipError_t e = hipModuleLoadData(&c.module, code.data());
-    if (e == hipSuccess) e = hipModuleGetFunction(&c.fn, c.module, "zmc_user_kernel");
-    if (e != hipSuccess) {
-        set_error(std::string("loading the user kernel: ") + hipGetErrorString(e));
-        return ZMC_EDEVICE;
     }
     int nb = 0, dev = 0, ncu = 0;
     if (hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(&nb, c.fn, kSampleThreads, 0) != hipSuccess || nb < 1)

@@ -110,23 +110,44 @@ __device__ __forceinline__ void corner(const SlotDesc& sd, int level, uint64_t u
 
 // The 4 samples of a thread's group take words s*D + i, s = 0..3, i < D:
 // Philox blocks cb .. cb + D - 1 (4 words each), generated in lockstep in the
-// source; the scheduler orders them by register need (see build.py).
+// source; the registry's kernels leave the order to a scheduler that goes by
+// register need (see build.py).  Run-time compiled kernels take the compiler's
+// own schedule, which keeps all of a lockstep's words live: with many
+// dimensions they generate the blocks in two halves (HALVES), those holding
+// samples 0-1, whose samples are evaluated, and then the rest.
 // eval(q, w) gets sample q's D words in order.
-template <int D, class Eval>
+template <int D, bool HALVES, class Eval>
 __device__ __forceinline__ void group_samples(uint32_t cb, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0,
                                               uint32_t k1, Eval&& eval)
 {
-    uint32_t c[D];
-    uint32_t w[4 * D];
+    constexpr int A = HALVES ? (D + 1) / 2 : D, B = D - A; // blocks of the first half (or all), of the second
+    constexpr int QA = HALVES ? 2 : 4;                     // samples that lie in the first alone
+    uint32_t ca[A], wa[4 * A];
 #pragma unroll
-    for (int k = 0; k < D; ++k) c[k] = cb + (uint32_t)k;
-    philox4x32_10_lockstep<D>(c, c1, c2, c3, k0, k1, w);
+    for (int k = 0; k < A; ++k) ca[k] = cb + (uint32_t)k;
+    philox4x32_10_lockstep<A>(ca, c1, c2, c3, k0, k1, wa);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
+    for (int q = 0; q < QA; ++q) {
         uint32_t ws[D];
 #pragma unroll
-        for (int i = 0; i < D; ++i) ws[i] = w[q * D + i];
+        for (int i = 0; i < D; ++i) ws[i] = wa[q * D + i];
         eval(q, ws);
+    }
+    if constexpr (HALVES) {
+        uint32_t cc[B], wb[4 * B];
+#pragma unroll
+        for (int k = 0; k < B; ++k) cc[k] = cb + (uint32_t)(A + k);
+        philox4x32_10_lockstep<B>(cc, c1, c2, c3, k0, k1, wb);
+#pragma unroll
+        for (int q = QA; q < 4; ++q) {
+            uint32_t ws[D];
+#pragma unroll
+            for (int i = 0; i < D; ++i) {
+                const int n = q * D + i;
+                ws[i] = n < 4 * A ? wa[n] : wb[n - 4 * A];
+            }
+            eval(q, ws);
+        }
     }
 }
 
@@ -170,7 +191,8 @@ struct CubeState<I, D, false> {
 // KEEP_S2: also accumulate the sum of squares (only the per-(cube, trial)
 // trace reads it; the estimator uses the sums alone).  Without it the
 // partial's second member is 0.
-template <class I, int D, bool FP32, bool KEEP_S2>
+// HALVES: see group_samples.
+template <class I, int D, bool FP32, bool KEEP_S2, bool HALVES = false>
 __device__ __forceinline__ void sample_units(const SampleArgs& a)
 {
     // blocks of 64, 128 or 256 threads (the tile table's block shape)
@@ -270,7 +292,7 @@ __device__ __forceinline__ void sample_units(const SampleArgs& a)
         auto group = [&](auto ragged, auto rounded, int nvalid) {
             constexpr bool kRagged = decltype(ragged)::value;
             [[maybe_unused]] float gs = 0.0f, gb = 0.0f;
-            group_samples<D>(cb, c1, c2, c3, k0, k1, [&](int q, const uint32_t* w) {
+            group_samples<D, HALVES>(cb, c1, c2, c3, k0, k1, [&](int q, const uint32_t* w) {
                 if constexpr (FP32) {
                     float v[D];
 #pragma unroll
