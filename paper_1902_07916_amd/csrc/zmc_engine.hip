@@ -532,7 +532,7 @@ int Engine::step(hipStream_t st, const std::vector<LiveSeg>& live, uint64_t* cur
     int nb = 0;
     struct Launch {
         int off, count, integrand, dim, eval;
-        int64_t units, unit_samples;
+        int64_t units, unit_samples; // points a unit, on average
         bool any_arg;
     };
     std::vector<Launch> launches;
@@ -544,9 +544,8 @@ int Engine::step(hipStream_t st, const std::vector<LiveSeg>& live, uint64_t* cur
         L.integrand = r0.integrand;
         L.dim = r0.dim;
         L.eval = r0.eval;
-        L.unit_samples = 256LL * groups_of(r0);
         L.any_arg = false;
-        int64_t u = 0;
+        int64_t u = 0, cap = 0; // units, and the points that they hold at most
         for (int i : kv.second) {
             const zmc_request& r = slots_[live[i].slot].req;
             L.any_arg |= slots_[live[i].slot].any_arg;
@@ -554,9 +553,14 @@ int Engine::step(hipStream_t st, const std::vector<LiveSeg>& live, uint64_t* cur
             h_bsegs_[nb].seg = i;
             h_bsegs_[nb].pad = 0;
             ++nb;
-            u += live[i].n_cubes * (int64_t)r.trials * nch_of(r);
+            const int64_t n = live[i].n_cubes * (int64_t)r.trials * nch_of(r);
+            u += n;
+            cap += n * 256LL * groups_of(r);
         }
         L.units = u;
+        // of the whole bucket, so that neither the kernel nor the cut into
+        // launches depends on which request comes first
+        L.unit_samples = u > 0 ? std::max<int64_t>(1, cap / u) : 1;
         launches.push_back(L);
     }
     int32_t* h_flags = (int32_t*)(h_tab_ + flags_offset(ns));
