@@ -336,8 +336,11 @@ __device__ __forceinline__ void sample_units(const SampleArgs& a)
         };
         // An FP32 value that ends in a product can be fused into the group's
         // sum, which then rounds once less (a sum of 256 points moves by some
-        // 1e-9).  Whether it is depends on the request alone: in full chunks
-        // up to D = 3, with a multiple of 4 points up to D = 9, never above.
+        // 1e-9).  Whether it may be depends on the request alone: in full
+        // chunks up to D = 3, with a multiple of 4 points up to D = 9, never
+        // above.  The lines lie where separate copies of this loop once had
+        // them, for the sake of the same bits.  Where it may be, the compiler's
+        // contraction does it: a body's last operation is not known here.
         constexpr bool kProduct = FP32 && I::kProduct;
         bool fused = false;
         if constexpr (kProduct && D <= 3) fused = pts == G * 256;
