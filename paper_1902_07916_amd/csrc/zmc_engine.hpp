@@ -95,9 +95,9 @@ struct TileTable {
     // So they run from 2048 points a unit (the bucket's mean) and 2^28 a
     // launch on, in every bucket: over the seven registry families, 1 to 16
     // dimensions, both modes and six sizes from 250 to 65536 points a cube no
-    // case was slower than in the build before these variants, whose table ran
-    // everywhere (1330 cases, 1.14 times as fast in the mean).  A tuning file's
-    // choice runs always.
+    // case is slower, beyond what repeated runs differ by, than in the build
+    // before these variants, whose table ran everywhere (1330 cases, 1.14 times
+    // as fast in the mean).  A tuning file's choice runs always.
     int waves(int integrand, int dim, int eval, int64_t units, int64_t unit_samples) const
     {
         if (integrand < 0 || integrand >= 8) return 0;
