@@ -358,8 +358,8 @@ int zmc_cube_estimates(const zmc_request* req, int level, const uint64_t* uids, 
  * Which of its products and sums are fused is the compiler's choice (in FP32 a
  * value can differ in its last bit between builds of the library).
  * The body is compiled with hipRTC for gfx950 now (to report errors) and once
- * per (D, eval) on first use (twice for an FP32 body of many registers below 8
- * dimensions, and again for traced calls); the returned id (>= 100) is then used as
+ * per (D, eval) on first use (twice for some FP32 bodies of many registers, and
+ * again for traced calls); the returned id (>= 100) is then used as
  * integrand_id / zmc_request.integrand with n_params params.  Does not need
  * zmc_init().  EINVAL: NULL arguments, n_params outside 0..34, a body that
  * does not compile (zmc_strerror(ZMC_EINVAL) holds the compiler log), or more

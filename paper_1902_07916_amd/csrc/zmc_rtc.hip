@@ -60,6 +60,14 @@ constexpr int kFourWavesRegs = 128;
 // spills 20 bytes for 84 (154 -> 158), and the same at D = 12 in FP64 140 for
 // 150 (180, 180); a body of D (D - 1) / 2 quotients at D = 16 22.3 -> 22.6.
 // At D = 8 and 9 halves gain 0-4% with bodies that spill and lose 0-3% with others.
+// An odd number of dimensions leaves words of the first half to the second, and
+// an FP32 body that spills under the bound is then tried once more with the
+// halves kept apart; the build that spills nothing is kept.  11- and 13-D
+// Gaussian bodies spill 28 and 64 bytes a lane one way and nothing the other,
+// 247 -> 255 and 211 -> 222, 11- and 13-D products of D factors 305 -> 312 and
+// 257 -> 266.  Kept apart at even D they lose 2-4% though the spills go
+// (Gaussian at 10-D 286 -> 276, at 12-D 244 -> 234), and so do bodies that
+// spill nothing (damped wave at 11- and 13-D 3% and 2%).
 constexpr int kHalvesMinD = 10;
 
 std::mutex g_mu;
@@ -74,13 +82,13 @@ typedef __hip_internal::int32_t int32_t;
 typedef __hip_internal::uint8_t uint8_t;
 )ZMCRTC";
 
-std::string program_source(const std::string& body, int dim, bool fp32, bool keep_s2, bool four_waves)
+std::string program_source(const std::string& body, int dim, bool fp32, bool keep_s2, bool four_waves, int halves)
 {
     std::string s = kPrelude;
     s += "#define ZMC_D " + std::to_string(dim) + "\n";
     s += "#define ZMC_FP32 " + std::string(fp32 ? "true" : "false") + "\n";
     s += "#define ZMC_OCCUPANCY " + std::string(four_waves ? "__attribute__((amdgpu_waves_per_eu(4)))" : "") + "\n";
-    s += "#define ZMC_HALVES " + std::string(dim >= kHalvesMinD ? "true" : "false") + "\n";
+    s += "#define ZMC_HALVES " + std::to_string(halves) + "\n";
     s += "#define ZMC_KEEP_S2 " + std::string(keep_s2 ? "true" : "false") + "\n";
     s += R"ZMCRTC(
 #include "zmc_sample_core.hpp"
@@ -159,10 +167,10 @@ extern "C" __global__ __launch_bounds__(256) ZMC_OCCUPANCY void zmc_user_kernel(
 
 // Compile one variant to a code object; returns 0 and fills `code`, or -1
 // with the compiler log in `log`.
-int compile(const std::string& body, int dim, bool fp32, bool keep_s2, bool four_waves, std::vector<char>& code,
-            std::string& log)
+int compile(const std::string& body, int dim, bool fp32, bool keep_s2, bool four_waves, int halves,
+            std::vector<char>& code, std::string& log)
 {
-    const std::string src = program_source(body, dim, fp32, keep_s2, four_waves);
+    const std::string src = program_source(body, dim, fp32, keep_s2, four_waves, halves);
     hiprtcProgram prog;
     if (hiprtcCreateProgram(&prog, src.c_str(), "zmc_user.hip", kRtcHeaderCount, kRtcHeaderSources,
                             kRtcHeaderNames) != HIPRTC_SUCCESS) {
@@ -206,7 +214,7 @@ int rtc_register(const char* body, int n_params, int* id)
     // compile once (D = 4, FP64) so that syntax errors surface now
     std::vector<char> code;
     std::string log;
-    if (compile(body, 4, false, false, false, code, log) != 0) {
+    if (compile(body, 4, false, false, false, 0, code, log) != 0) {
         set_error("user integrand does not compile:\n" + log);
         return ZMC_EINVAL;
     }
@@ -250,27 +258,38 @@ static int rtc_get(int id, int dim, int eval, bool keep_s2, Compiled& out)
         body = g_defs[k].body;
     }
     const bool fp32 = eval == ZMC_EVAL_FP32;
-    bool four_waves = fp32 && dim >= kFourWavesMinD;
-    Compiled c;
-    while (true) {
+    auto load = [&](bool four_waves, int halves, Compiled& k) -> int {
         std::vector<char> code;
         std::string log;
-        if (compile(body, dim, fp32, keep_s2, four_waves, code, log) != 0) {
+        if (compile(body, dim, fp32, keep_s2, four_waves, halves, code, log) != 0) {
             set_error("user integrand does not compile:\n" + log);
             return ZMC_EINVAL;
         }
-        hipError_t e = hipModuleLoadData(&c.module, code.data());
-        if (e == hipSuccess) e = hipModuleGetFunction(&c.fn, c.module, "zmc_user_kernel");
+        hipError_t e = hipModuleLoadData(&k.module, code.data());
+        if (e == hipSuccess) e = hipModuleGetFunction(&k.fn, k.module, "zmc_user_kernel");
         if (e != hipSuccess) {
             set_error(std::string("loading the user kernel: ") + hipGetErrorString(e));
             return ZMC_EDEVICE;
         }
-        int regs = 0;
-        if (!fp32 || four_waves || hipFuncGetAttribute(&regs, HIP_FUNC_ATTRIBUTE_NUM_REGS, c.fn) != hipSuccess ||
-            regs <= kFourWavesRegs)
-            break;
+        return ZMC_OK;
+    };
+    auto attribute = [](const Compiled& k, hipFunction_attribute a) {
+        int v = 0;
+        return hipFuncGetAttribute(&v, a, k.fn) == hipSuccess ? v : 0;
+    };
+    const int halves = dim >= kHalvesMinD ? 1 : 0;
+    Compiled c;
+    const int rc = load(fp32 && dim >= kFourWavesMinD, halves, c);
+    if (rc != ZMC_OK) return rc;
+    // a second build, kept where it serves; should it fail, the first stands
+    const bool bound = fp32 && dim < kFourWavesMinD && attribute(c, HIP_FUNC_ATTRIBUTE_NUM_REGS) > kFourWavesRegs;
+    const bool apart =
+        fp32 && halves && dim % 2 == 1 && attribute(c, HIP_FUNC_ATTRIBUTE_LOCAL_SIZE_BYTES) > 0;
+    Compiled b;
+    if ((bound || apart) && load(true, apart ? 2 : halves, b) == ZMC_OK) {
+        if (apart && attribute(b, HIP_FUNC_ATTRIBUTE_LOCAL_SIZE_BYTES) > 0) std::swap(b, c);
         (void)hipModuleUnload(c.module);
-        four_waves = true;
+        c = b;
     }
     std::lock_guard<std::mutex> lk(g_mu);
     auto it = g_cache.find(key);

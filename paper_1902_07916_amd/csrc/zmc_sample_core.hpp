@@ -113,10 +113,11 @@ __device__ __forceinline__ void corner(const SlotDesc& sd, int level, uint64_t u
 // source; the registry's kernels leave the order to a scheduler that goes by
 // register need (see build.py).  Run-time compiled kernels take the compiler's
 // own schedule, which keeps all of a lockstep's words live: with many
-// dimensions they generate the blocks in two halves (HALVES), those holding
-// samples 0-1, whose samples are evaluated, and then the rest.
+// dimensions they generate the blocks in two halves (HALVES = 1), those holding
+// samples 0-1, whose samples are evaluated, and then the rest; HALVES = 2 also
+// bars the scheduler from moving instructions between the two.
 // eval(q, w) gets sample q's D words in order.
-template <int D, bool HALVES, class Eval>
+template <int D, int HALVES, class Eval>
 __device__ __forceinline__ void group_samples(uint32_t cb, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0,
                                               uint32_t k1, Eval&& eval)
 {
@@ -134,6 +135,7 @@ __device__ __forceinline__ void group_samples(uint32_t cb, uint32_t c1, uint32_t
         eval(q, ws);
     }
     if constexpr (HALVES) {
+        if constexpr (HALVES == 2) __builtin_amdgcn_sched_barrier(0);
         uint32_t cc[B], wb[4 * B];
 #pragma unroll
         for (int k = 0; k < B; ++k) cc[k] = cb + (uint32_t)(A + k);
@@ -148,6 +150,18 @@ __device__ __forceinline__ void group_samples(uint32_t cb, uint32_t c1, uint32_t
             }
             eval(q, ws);
         }
+    }
+}
+
+// a + b; unless FUSED, a product that one of them is rounds before it.
+template <bool FUSED>
+__device__ __forceinline__ float group_add(float a, float b)
+{
+    if constexpr (FUSED) {
+        return a + b;
+    } else {
+#pragma clang fp contract(off)
+        return a + b;
     }
 }
 
@@ -192,7 +206,7 @@ struct CubeState<I, D, false> {
 // trace reads it; the estimator uses the sums alone).  Without it the
 // partial's second member is 0.
 // HALVES: see group_samples.
-template <class I, int D, bool FP32, bool KEEP_S2, bool HALVES = false>
+template <class I, int D, bool FP32, bool KEEP_S2, int HALVES = 0>
 __device__ __forceinline__ void sample_units(const SampleArgs& a)
 {
     // blocks of 64, 128 or 256 threads (the tile table's block shape)
@@ -298,15 +312,18 @@ __device__ __forceinline__ void sample_units(const SampleArgs& a)
 #pragma unroll
                     for (int i = 0; i < D; ++i) v[i] = unit_interval_f32(w[i]);
                     float f = I::f32(cs.p, v);
-                    if constexpr (decltype(rounded)::value) asm("" : "+v"(f));
+                    // rounded by an opaque move, or (HALVES = 2) by sums that may not be fused
+                    constexpr bool kFree = !(decltype(rounded)::value && HALVES == 2);
+                    auto add = [](float a, float b) { return group_add<kFree>(a, b); };
+                    if constexpr (decltype(rounded)::value && HALVES != 2) asm("" : "+v"(f));
                     if constexpr (kRagged) f = (q < nvalid) ? f : 0.0f;
                     if constexpr (kPairSum) {
                         if (q == 0) gs = f;
-                        else if (q == 1) gs = gs + f;
+                        else if (q == 1) gs = add(gs, f);
                         else if (q == 2) gb = f;
-                        else gb = gb + f;
+                        else gb = add(gb, f);
                     } else {
-                        gs = q == 0 ? f : gs + f;
+                        gs = q == 0 ? f : add(gs, f);
                     }
                     if constexpr (KEEP_S2) {
                         const double fd = (double)f;

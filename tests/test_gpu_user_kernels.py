@@ -1,6 +1,7 @@
 """Run-time compiled kernels on both sides of what their build depends on: from
 10 dimensions on a group's words are generated in two halves, and an FP32 body
-of many registers is compiled a second time with a register bound."""
+of many registers is compiled a second time, with a register bound or with the
+halves kept apart."""
 import os
 import sys
 
@@ -56,4 +57,24 @@ def test_bodies_of_many_registers(z, dim):
     a, b = z.integrate(uid, **w, eval="fp32"), z.integrate(uid, **w, eval="fp64")
     t = z.integrate(uid, **w, eval="fp32", trace=True, trace_capacity=1 << 10)
     assert abs(a.integral - b.integral) <= (12 * dim + dim * dim) * 2.0 ** -24 * b.integral
+    assert (a.integral, a.std) == (t.integral, t.std)
+
+
+@pytest.mark.parametrize("samples", [1024, 1027, 200])
+@pytest.mark.parametrize("dim", [11, 13])
+def test_halves_kept_apart(z, dim, samples):
+    """An FP32 Gaussian body, whose first build spills at 11 and 13 dimensions:
+    the kept build against the FP64 estimate of the same points, and against
+    the traced kernel, which is built by itself."""
+    import paper_1902_07916_amd as pkg
+    uid = pkg.register_integrand("real q = 0; for (int i = 0; i < D; ++i) { real d = x[i] - (real)p[1]; q += d * d; } "
+                                 "return exp(-q / (real)(2 * p[0] * p[0]));", 2)
+    print("user kernels: apart", dim, samples, flush=True)
+    w = dict(params=[1.0, 0.4], lower=[0.0] * dim, upper=[1.0] * dim, divisions=1, samples=samples, trials=3,
+             max_depth=0, sigma_mult=1.0, seed=5)
+    a, b = z.integrate(uid, **w, eval="fp32"), z.integrate(uid, **w, eval="fp64")
+    t = z.integrate(uid, **w, eval="fp32", trace=True, trace_capacity=16)
+    # q <= 0.36 D takes D + 1 roundings in sequence and each d one, exp's argument
+    # one more and exp itself a few; the group's sums two
+    assert abs(a.integral - b.integral) <= (0.18 * dim * (dim + 5) + 8) * 2.0 ** -24 * b.integral
     assert (a.integral, a.std) == (t.integral, t.std)
